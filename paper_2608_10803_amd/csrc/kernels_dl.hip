@@ -82,7 +82,6 @@ struct Dl {
   static constexpr int WPE = (S * (BM + BN) * BK * 2 <= 80 * 1024 && BM * BN <= 256 * 128) ? 2 : 1;
   static_assert(BM % 32 == 0 && BM >= 32 && BN >= 128 && BN <= 512 && (BK == 32 || BK == 64) && WTN % 32 == 0,
                 "tile");
-  static_assert(3 * LOADS <= 63, "vmcnt range");
   // the bf16 epilogue's per-wave slab of 32 output rows goes into one stage
   // buffer per wave: A0, A1, B0, B1 if both kinds are large enough, else
   // the first four of the kind that is, else two slabs in each of B0, B1
@@ -100,23 +99,17 @@ struct Dl {
 // and 64 banks.
 __device__ __forceinline__ int swz_b(int r) { return (0xAC60 >> (4 * (r & 3))) & 15; }
 
-// Workgroup barrier of the pipeline: this wave waits until at most `ahead`
-// (0 .. 3) later stages of its own loads are in flight and its LDS reads
-// are done, then all waves meet. After it every wave's loads of the stage
-// about to be read have landed and no wave still reads the stage about to be
-// reloaded. (__syncthreads would add a workgroup fence, which waits for ALL
-// loads into LDS, the prefetched stages included.) The empty asm with a
-// memory clobber keeps the compiler from moving LDS accesses across it.
-template <int LOADS>
-__device__ __forceinline__ void stage_barrier(int ahead) {
-  if (ahead <= 0)
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-  else if (ahead == 1)
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS));
-  else if (ahead == 2)
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * LOADS));
-  else
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * LOADS));
+// Workgroup barrier of the pipeline: this wave waits until at most N of its
+// loads into LDS are in flight and its own LDS reads and writes are done,
+// then all waves meet. After it every wave's older loads have landed and no
+// wave still reads what it read before. (__syncthreads would add a workgroup
+// fence, which waits for ALL loads into LDS, the prefetched stages included.)
+// The empty asm with a memory clobber keeps the compiler from moving LDS
+// accesses across it.
+template <int N>
+__device__ __forceinline__ void stage_barrier() {
+  static_assert(N >= 0 && N <= 63, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(N));
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
@@ -129,12 +122,13 @@ struct DlTile {
   const char* b;  // B + n0
   int64_t ldb2;
   int64_t K, kB;  // k of the loop (A's columns), rows of B
+  int w;          // wave (uniform)
   int32_t a_off[G::NIA], b_off[G::NIB];
-  int32_t a_k[G::NIA], b_k[G::NIB];
+  int32_t a_k[G::NIA], b_k0;
 
   __device__ __forceinline__ void init(const GemmArgs& g, int64_t m0, int64_t n0) {
     const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     a = reinterpret_cast<const char*>(g.A + m0 * g.lda);
     b = reinterpret_cast<const char*>(g.B + n0);
     ldb2 = g.ldb * 2;
@@ -149,63 +143,58 @@ struct DlTile {
       a_off[q] = row < rows ? (int32_t)(row * g.lda * 2) + c * 16 : OOB_OFF;
       a_k[q] = c * 8;
     }
+    b_k0 = lane / G::B_LPR;
 #pragma unroll
     for (int q = 0; q < G::NIB; ++q) {
-      const int u = w * G::NIB + q;
-      const int kr = u * G::B_RPI + lane / G::B_LPR;
+      const int kr = (w * G::NIB + q) * G::B_RPI + b_k0;
       const int c = (lane % G::B_LPR) ^ swz_b(kr);
       b_off[q] = c * 8 < cols ? (int32_t)(kr * g.ldb * 2) + c * 16 : OOB_OFF;
-      b_k[q] = kr;
     }
   }
 };
 
-// This wave's share of the loads of one k-block (starting at k0) into one
-// stage: NIA loads of A, then NIB loads of B, issued one at a time so that
-// they can be spread between MFMAs. A block past K (the pipeline's tail)
-// loads nothing: every offset is out of range, the stage gets zeros that no
-// step reads.
+// This wave's share of the loads of one k-block into one stage: NIA loads of
+// A, then NIB loads of B, issued one at a time so that they can be spread
+// between MFMAs. The blocks are taken in order from `kbeg` on; what a block
+// has past the partition's end (the k tail, or a whole block past it) is out
+// of range and read as zeros. A step to the next block is a few scalar
+// additions: a wave issues one instruction at a time, and the MFMAs wait for
+// whatever scalar work stands in front of them.
 template <class G>
 struct StageLoads {
-  __amdgpu_buffer_rsrc_t ra, rb;
+  const char* pa;  // the block's first k of A's tile, and of B's
+  const char* pb;
+  int remA, remB;  // k of A, rows of B from there to the partition's end
   char* sA;
   char* sB;
-  int krem, kremB;
-  bool full, fullB;
-  __device__ __forceinline__ void init(char* a_stage, char* b_stage, const DlTile<G>& t, int64_t k0) {
-    const int64_t kleft = t.K - k0, kleftB = t.kB - k0;
-    krem = kleft < G::BK ? (int)(kleft > 0 ? kleft : 0) : G::BK;  // k of A in this block (uniform)
-    kremB = kleftB < G::BK ? (int)(kleftB > 0 ? kleftB : 0) : G::BK;  // rows of B in this block
-    full = krem == G::BK;  // only a K tail needs the per-chunk test
-    fullB = kremB == G::BK;
-    ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(t.a) + k0 * 2, (short)0, (int)0x7FFFFFF0,
-                                           (int)RSRC_WORD3);
-    rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(t.b) + k0 * t.ldb2, (short)0, (int)0x7FFFFFF0,
-                                           (int)RSRC_WORD3);
-    sA = a_stage;
-    sB = b_stage;
+  __device__ __forceinline__ void start(const DlTile<G>& t, int64_t kbeg, int64_t kstop) {
+    pa = t.a + kbeg * 2;
+    pb = t.b + kbeg * t.ldb2;
+    remA = (int)(min(kstop, t.K) - kbeg);
+    remB = (int)(min(kstop, t.kB) - kbeg);
+  }
+  __device__ __forceinline__ void next(const DlTile<G>& t) {
+    pa += G::BK * 2;
+    pb += G::BK * t.ldb2;
+    remA -= G::BK;
+    remB -= G::BK;
   }
   // load q of this wave (0 .. NIA + NIB - 1; a compile-time index)
   __device__ __forceinline__ void issue(const DlTile<G>& t, int q) const {
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (q < G::NIA) {
-      const int32_t off = full || t.a_k[q] < krem ? t.a_off[q] : OOB_OFF;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void*)(sA + (w * G::NIA + q) * 1024), 16, off, 0, 0, 0);
+      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(pa), (short)0,
+                                                                         (int)0x7FFFFFF0, (int)RSRC_WORD3);
+      const int32_t off = t.a_k[q] < remA ? t.a_off[q] : OOB_OFF;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(sA + (t.w * G::NIA + q) * 1024), 16, off, 0, 0, 0);
     } else {
       const int qb = q - G::NIA;
-      const int32_t off = fullB || t.b_k[qb] < kremB ? t.b_off[qb] : OOB_OFF;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(sB + (w * G::NIB + qb) * 1024), 16, off, 0, 0, 0);
+      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(pb), (short)0,
+                                                                         (int)0x7FFFFFF0, (int)RSRC_WORD3);
+      const int32_t off = t.b_k0 < remB - (t.w * G::NIB + qb) * G::B_RPI ? t.b_off[qb] : OOB_OFF;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(sB + (t.w * G::NIB + qb) * 1024), 16, off, 0, 0, 0);
     }
   }
 };
-
-template <class G>
-__device__ __forceinline__ void issue_stage(char* sA, char* sB, const DlTile<G>& t, int64_t k0) {
-  StageLoads<G> L;
-  L.init(sA, sB, t, k0);
-#pragma unroll
-  for (int q = 0; q < G::LOADS; ++q) L.issue(t, q);
-}
 
 // ---- loads through registers (any alignment, K >= 8 and N >= 8)
 // The same chunks into the same LDS slots as the direct loads, fetched with
@@ -307,31 +296,51 @@ struct Frags {
   u32x4 a[G::TM], b[G::TN];
 };
 
+// Byte offsets of a lane's fragment reads within a stage, computed once: one
+// per k-step for A (its rows are BK * 2 bytes apart, the swizzle of row 32 i +
+// l32 is that of l32), one per column fragment for B (k-step and half are
+// constant offsets: the swizzle only depends on the k-row mod 4).
 template <class G>
-__device__ __forceinline__ void read_frags(const char* sA, const char* sB, int ks, int wr, int wc, Frags<G>& f) {
-  const int lane = threadIdx.x & 63;
-  const int l32 = lane & 31, hi = lane >> 5, i16 = lane & 15, g = lane >> 4;
+struct FragAddr {
+  int a[G::BK / 16], b[G::TN];
+  __device__ __forceinline__ void init(int wr, int wc) {
+    const int lane = threadIdx.x & 63;
+    const int l32 = lane & 31, hi = lane >> 5, i16 = lane & 15, g = lane >> 4;
 #pragma unroll
-  for (int i = 0; i < G::TM; ++i) {
-    const int row = wr * G::WTM + 32 * i + l32;
-    const int ch = 2 * ks + hi;  // 8 consecutive k of the lane's k-group
-    f.a[i] = *reinterpret_cast<const u32x4*>(sA + row * (G::BK * 2) + ((ch ^ swz_a<G::BK>(row)) << 4));
+    for (int ks = 0; ks < G::BK / 16; ++ks) {
+      const int ch = 2 * ks + hi;  // 8 consecutive k of the lane's k-group
+      a[ks] = (wr * G::WTM + l32) * (G::BK * 2) + ((ch ^ swz_a<G::BK>(l32)) << 4);
+      // opaque: a sum the compiler may not take apart into a chain of
+      // address steps, at whose end it no longer knows which stage is read
+      // (and would wait for the loads into all of them)
+      asm("" : "+v"(a[ks]));
+    }
+    // the transpose read of a 16-lane group covers 4 k-rows x 16 columns: lane
+    // i16 addresses k-row i16 >> 2 and columns 4 * (i16 & 3) .. +3 and receives
+    // column i16 of the 4 rows; groups 0 / 1 take columns 0-15 / 16-31 of the
+    // fragment at the lane's k-group 0, groups 2 / 3 the same at k-group 1
+    const int kr0 = 8 * (g >> 1) + (i16 >> 2);
+#pragma unroll
+    for (int j = 0; j < G::TN; ++j) {
+      const int col = wc * G::WTN + 32 * j + 16 * (g & 1) + (i16 & 3) * 4;
+      b[j] = kr0 * (G::BN_ * 2) + ((col >> 3) ^ swz_b(kr0)) * 16 + (col & 7) * 2;
+      asm("" : "+v"(b[j]));
+    }
   }
-  // the transpose read of a 16-lane group covers 4 k-rows x 16 columns: lane
-  // i16 addresses k-row i16 >> 2 and columns 4 * (i16 & 3) .. +3 and receives
-  // column i16 of the 4 rows; groups 0 / 1 take columns 0-15 / 16-31 of the
-  // fragment at the lane's k-group 0, groups 2 / 3 the same at k-group 1
-  const int kr0 = 8 * (g >> 1) + (i16 >> 2);
-  const int sw = swz_b(kr0);  // every k-row the lane reads is kr0 mod 4
+};
+
+template <class G>
+__device__ __forceinline__ void read_frags(const char* sA, const char* sB, int ks, const FragAddr<G>& at, Frags<G>& f) {
+#pragma unroll
+  for (int i = 0; i < G::TM; ++i)
+    f.a[i] = *reinterpret_cast<const u32x4*>(sA + at.a[ks] + 32 * i * (G::BK * 2));
 #pragma unroll
   for (int j = 0; j < G::TN; ++j) {
-    const int col = wc * G::WTN + 32 * j + 16 * (g & 1) + (i16 & 3) * 4;
-    const int cb = ((col >> 3) ^ sw) * 16 + (col & 7) * 2;
     uint32_t v[4];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int kr = 16 * ks + 4 * h + kr0;
-      const tr16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr16x4*)(sB + kr * (G::BN_ * 2) + cb));
+      const tr16x4 r =
+          __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr16x4*)(sB + at.b[j] + (16 * ks + 4 * h) * (G::BN_ * 2)));
       const uint64_t bits = __builtin_bit_cast(uint64_t, r);
       v[2 * h] = (uint32_t)bits;
       v[2 * h + 1] = (uint32_t)(bits >> 32);
@@ -340,44 +349,28 @@ __device__ __forceinline__ void read_frags(const char* sA, const char* sB, int k
   }
 }
 
-// Multiplies out one stage: BK / 16 k-steps, TM x TN MFMAs each, while the
-// next stage's loads go out. The reads of step ks + 1 are issued before the
-// MFMAs of step ks (two fragment sets), so their latency runs under those
-// MFMAs; the next stage's global loads are spread one per MFMA over the
-// steps instead of leaving in one burst (a burst fills the load queue, and
-// a wave stalled on a full queue issues no MFMAs). The scheduling barriers
-// keep the compiler to this order.
-template <class G, class Loads, class Tile>
-__device__ __forceinline__ void compute_stage(const char* sA, const char* sB, f32x16 (&acc)[G::TM][G::TN],
-                                              int wr, int wc, Loads& nxt, const Tile& t) {
-  constexpr int KS = G::BK / 16, NMF = G::TM * G::TN;
-  // next-stage loads per k-step: with two stages the loads must land
-  // within this stage, so they all go out as early as possible (one per
-  // MFMA from the first step on); with more stages they are spread evenly
-  constexpr int LPS = G::S == 2 ? NMF : (G::LOADS + KS - 1) / KS;
-  static_assert(G::S > 2 || G::LOADS <= KS * NMF, "one load per MFMA at most");
-  Frags<G> f[2];
-  read_frags<G>(sA, sB, 0, wr, wc, f[0]);
-  __builtin_amdgcn_sched_barrier(0);  // step 0's reads first: its MFMAs wait for those only
+// What runs under the NMF MFMAs of one k-step: RD LDS reads (the next step's
+// fragments), two to an MFMA from the first one on, and LD global loads one
+// to an MFMA. A wave that stalls on a full LDS or load queue issues no MFMAs,
+// so neither may leave in a burst.
+template <int NMF, int RD, int LD>
+__device__ __forceinline__ void interleave_step() {
+  constexpr int RPM = 2 * NMF >= RD ? 2 : (RD + NMF - 1) / NMF, LPM = (LD + NMF - 1) / NMF;
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    Frags<G>& cur = f[ks & 1];
-    if (ks + 1 < KS) read_frags<G>(sA, sB, ks + 1, wr, wc, f[(ks + 1) & 1]);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < G::TM; ++i)
-#pragma unroll
-      for (int j = 0; j < G::TN; ++j) acc[i][j] = mfma32(cur.b[j], cur.a[i], acc[i][j]);  // C^T: a lane holds a row of C
-#pragma unroll
-    for (int q = ks * LPS; q < (ks + 1) * LPS && q < G::LOADS; ++q) nxt.issue(t, q);
-#pragma unroll
-    for (int m = 0; m < NMF; ++m) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-      if (m < LPS && ks * LPS + m < G::LOADS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // one load
-    }
-    __builtin_amdgcn_sched_barrier(0);
+  for (int m = 0; m < NMF; ++m) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                      // one MFMA
+    if (m * RPM < RD) __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);  // LDS reads
+    if ((m + 1) * LD / NMF > m * LD / NMF) __builtin_amdgcn_sched_group_barrier(0x020, LPM, 0);  // loads
   }
-  if constexpr (std::is_same<Loads, RegLoads<G>>::value) nxt.finish();  // registers -> the next stage
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+template <class G>
+__device__ __forceinline__ void mfma_step(const Frags<G>& f, f32x16 (&acc)[G::TM][G::TN]) {
+#pragma unroll
+  for (int i = 0; i < G::TM; ++i)
+#pragma unroll
+    for (int j = 0; j < G::TN; ++j) acc[i][j] = mfma32(f.b[j], f.a[i], acc[i][j]);  // C^T: a lane holds a row of C
 }
 
 // One output tile (tile coordinates tm, tn) over K partition `split` of the
@@ -429,53 +422,150 @@ __device__ __forceinline__ void dl_tile(const GemmArgs& g, int tm, int tn, int s
     constexpr int I = decltype(ic)::value;
     return I == 0 ? lB0 : I == 1 ? lB1 : I == 2 ? lB2 : I == 3 ? lB3 : lB4;
   };
-  // Every step issues one stage of loads (past the partition's last block:
-  // out-of-range loads), so at step kb exactly S - 2 stages of this wave's
-  // loads were issued after those of block kb.
+  // k of block b of the partition; past its last block K, where every load
+  // is out of range
   const int64_t kstop = kbeg + (int64_t)nk * G::BK;  // the partition's end, rounded up to a block
   auto kpos = [&](int b) { const int64_t k = kbeg + (int64_t)b * G::BK; return k < kstop ? k : t.K; };
-  auto prologue = [&](char* a_st, char* b_st, int64_t k) {
-    Loads L;
-    L.init(a_st, b_st, t, k);
-#pragma unroll
-    for (int q = 0; q < G::LOADS; ++q) L.issue(t, q);
-    if constexpr (RG) L.finish();
-  };
+
+  // The pipeline. A block's fragments are read one k-step ahead of their
+  // MFMAs, also across blocks: before the last k-step of block kb the waves
+  // meet (its fragments are in registers by then, and block kb + 1 has
+  // landed), the first fragments of block kb + 1 are read under that step's
+  // MFMAs, and block kb + S starts to load into the stage just freed. So no
+  // MFMA waits for an LDS read issued after a barrier: with the reads at the
+  // start of each block, after its barrier, the four waves' 32 KB of first
+  // fragments (256 clocks of LDS time) were exposed per 2060 clocks of MFMAs
+  // on the 256 x 256 x 64 tile.
+  constexpr int KS = G::BK / 16, NMF = G::TM * G::TN, RD = G::TM + 2 * G::TN;
+  // loads of a block per k-step, from the barrier on: with two stages over the
+  // first half of a block's MFMAs (they must land within the other half),
+  // with more stages over all of them. 8192^3 on the 256 x 256 x 64 tile: all
+  // in one step 855 us, over two 827, three 836, four 907.
+  constexpr int LSTEPS = S == 2 ? (KS + 1) / 2 : KS;
+  constexpr int LPS = RG ? G::LOADS : (G::LOADS + LSTEPS - 1) / LSTEPS;
+  constexpr int REST = G::LOADS - LPS;  // loads left for the next block's k-steps
+  FragAddr<G> fa;
+  fa.init(wr, wc);
+  Frags<G> f[2];
+  Loads nxt;
   if (nk > 0) {
-    prologue(lA0, lB0, kpos(0));
-    if constexpr (S > 2) prologue(lA1, lB1, kpos(1));
-    if constexpr (S > 3) prologue(lA2, lB2, kpos(2));
-    if constexpr (S > 4) prologue(lA3, lB3, kpos(3));
+    if constexpr (RG) {
+      Loads pro[S];
+#pragma unroll
+      for (int p = 0; p < S; ++p) {
+        pro[p].init(p == 0 ? lA0 : p == 1 ? lA1 : p == 2 ? lA2 : p == 3 ? lA3 : lA4,
+                    p == 0 ? lB0 : p == 1 ? lB1 : p == 2 ? lB2 : p == 3 ? lB3 : lB4, t, kpos(p));
+#pragma unroll
+        for (int q = 0; q < G::LOADS; ++q) pro[p].issue(t, q);
+      }
+#pragma unroll
+      for (int p = 0; p < S; ++p) pro[p].finish();
+      nxt.init(lA0, lB0, t, kpos(S));
+#pragma unroll
+      for (int q = 0; q < G::LOADS; ++q) nxt.issue(t, q);
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    } else {
+      nxt.start(t, kbeg, kstop);
+#pragma unroll
+      for (int p = 0; p < S; ++p) {
+        if (p > 0) nxt.next(t);
+        nxt.sA = p == 0 ? lA0 : p == 1 ? lA1 : p == 2 ? lA2 : p == 3 ? lA3 : lA4;
+        nxt.sB = p == 0 ? lB0 : p == 1 ? lB1 : p == 2 ? lB2 : p == 3 ? lB3 : lB4;
+#pragma unroll
+        for (int q = 0; q < (p == S - 1 ? LPS : G::LOADS); ++q) nxt.issue(t, q);
+      }
+      stage_barrier<(S - 1) * G::LOADS - REST>();
+    }
+    read_frags<G>(lA0, lB0, 0, fa, f[0]);
+    __builtin_amdgcn_sched_barrier(0);
   }
 
-  auto step = [&](auto ic, int kb) {
-    constexpr int I = decltype(ic)::value;
-    constexpr int NX = (I + S - 1) % S;  // stage that receives block kb + S - 1
-    stage_barrier<G::LOADS>(RG ? 0 : S - 2);
-    Loads nxt;
-    nxt.init(stA(std::integral_constant<int, NX>{}), stB(std::integral_constant<int, NX>{}), t, kpos(kb + S - 1));
-    compute_stage<G>(stA(ic), stB(ic), acc, wr, wc, nxt, t);
+  // k-steps 0 .. KS - 2 of the block in stage I; MORE: the rest of the loads
+  // of the block issued last
+  auto head = [&](auto ic, auto more) {
+    if constexpr (decltype(more)::value && REST > 0) {
+      // the stage they go to, as a constant: a pointer carried round the loop
+      // would hide from the compiler which stage it is, and every read of
+      // another stage would wait for these loads
+      const std::integral_constant<int, (decltype(ic)::value + S - 1) % S> pv{};
+      nxt.sA = stA(pv);
+      nxt.sB = stB(pv);
+    }
+#pragma unroll
+    for (int ks = 0; ks + 1 < KS; ++ks) {
+      read_frags<G>(stA(ic), stB(ic), ks + 1, fa, f[(ks + 1) & 1]);
+      mfma_step<G>(f[ks & 1], acc);
+      if constexpr (decltype(more)::value && REST > 0) {
+#pragma unroll
+        for (int q = (ks + 1) * LPS; q < (ks + 2) * LPS && q < G::LOADS; ++q) nxt.issue(t, q);
+        interleave_step<NMF, RD, LPS>();
+      } else {
+        interleave_step<NMF, RD, 0>();
+      }
+    }
   };
-  // whole groups of S blocks, then the remaining 0 .. S-1 blocks
+  // the barrier and the last k-step of block kb in stage I, with the first
+  // reads of the next block and the first loads of block kb + S
+  auto tail = [&](auto ic, int kb) {
+    constexpr int I = decltype(ic)::value;
+    const std::integral_constant<int, (I + 1) % S> nx{};
+    if constexpr (RG) {
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      nxt.sA = stA(ic);
+      nxt.sB = stB(ic);
+      nxt.finish();  // block kb + S, loaded during the last block
+      nxt.init(stA(ic), stB(ic), t, kpos(kb + S + 1));
+    } else {
+      stage_barrier<(S - 2) * G::LOADS>();
+      nxt.next(t);
+      nxt.sA = stA(ic);
+      nxt.sB = stB(ic);
+    }
+    read_frags<G>(stA(nx), stB(nx), 0, fa, f[0]);
+    mfma_step<G>(f[(KS - 1) & 1], acc);
+#pragma unroll
+    for (int q = 0; q < LPS; ++q) nxt.issue(t, q);
+    interleave_step<NMF, RD, LPS>();
+  };
+  auto step = [&](auto ic, int kb) {
+    head(ic, std::true_type{});
+    tail(ic, kb);
+  };
+  // the last blocks (at most S, all loading or loaded): block I of them
+  auto last = [&](auto ic, int left) {
+    constexpr int I = decltype(ic)::value;
+    if (I >= left) return;
+    head(ic, std::integral_constant<bool, I == 0>{});
+    if (I + 1 < left) {
+      const std::integral_constant<int, (I + 1) % S> nx{};
+      if constexpr (RG)
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      else
+        stage_barrier<(S - 2 - I > 0 ? S - 2 - I : 0) * G::LOADS>();
+      read_frags<G>(stA(nx), stB(nx), 0, fa, f[0]);
+    }
+    mfma_step<G>(f[(KS - 1) & 1], acc);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // groups of S blocks while more than S are left, then the rest
   int kb = 0;
-  for (; kb + S <= nk; kb += S) {
+  for (; nk - kb > S; kb += S) {
     step(std::integral_constant<int, 0>{}, kb);
     step(std::integral_constant<int, 1>{}, kb + 1);
     if constexpr (S > 2) step(std::integral_constant<int, 2>{}, kb + 2);
     if constexpr (S > 3) step(std::integral_constant<int, 3>{}, kb + 3);
     if constexpr (S > 4) step(std::integral_constant<int, 4>{}, kb + 4);
   }
-  if (kb < nk) step(std::integral_constant<int, 0>{}, kb);
-  if (kb + 1 < nk) step(std::integral_constant<int, 1>{}, kb + 1);
-  if constexpr (S > 3)
-    if (kb + 2 < nk) step(std::integral_constant<int, 2>{}, kb + 2);
-  if constexpr (S > 4)
-    if (kb + 3 < nk) step(std::integral_constant<int, 3>{}, kb + 3);
+  last(std::integral_constant<int, 0>{}, nk - kb);
+  last(std::integral_constant<int, 1>{}, nk - kb);
+  if constexpr (S > 2) last(std::integral_constant<int, 2>{}, nk - kb);
+  if constexpr (S > 3) last(std::integral_constant<int, 3>{}, nk - kb);
+  if constexpr (S > 4) last(std::integral_constant<int, 4>{}, nk - kb);
 
   // ---- epilogue
   const int64_t rbase = m0 + wr * G::WTM, cbase = n0 + wc * G::WTN;
   if constexpr (OUT == DL_BF16) {
-    stage_barrier<G::LOADS>(0);  // every wave's last reads of the stages are done
+    stage_barrier<0>();  // every wave's last reads of the stages are done, no load into them is in flight
     // the wave's slab: 32 rows x WTN bf16 in one of the stage buffers
     char* slab;
     if constexpr (G::SLAB_KIND == 0)
@@ -522,6 +612,7 @@ __device__ __forceinline__ void dl_tile(const GemmArgs& g, int tm, int tn, int s
       __builtin_amdgcn_sched_barrier(0);  // slab by slab: bounded live registers
     }
   } else {
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // no load into LDS outlives the workgroup
     float* dst = OUT == DL_PARTIAL ? g.ws + (size_t)split * (size_t)g.M * (size_t)g.ldw : static_cast<float*>(g.C);
     const int64_t ld = OUT == DL_PARTIAL ? g.ldw : g.ldc;
 #pragma unroll
@@ -557,6 +648,10 @@ __device__ __forceinline__ void dl_kernel(const GemmArgs& g) {
   if (g.swizzle) tile = xcd_remap(tile, ntiles);
   int tm, tn;
   tile_coords(tile, g.tiles_m, g.tiles_n, g.swizzle, tm, tn);
+  // the division ran in vector registers: back to scalar ones, or the
+  // operand pointers stay there and every load loops over its lanes' pointers
+  tm = __builtin_amdgcn_readfirstlane(tm);
+  tn = __builtin_amdgcn_readfirstlane(tn);
   dl_tile<BM, BN, BK, S, OUT, RG>(g, tm, tn, (int)blockIdx.y);
 }
 
@@ -589,7 +684,7 @@ template <int BM, int BN, int BK, int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Dl<BM, BN, BK, S>::WPE, Dl<BM, BN, BK, S>::WPE)))
 void k_dl_sc(GemmArgs g) {
   const int sup = blockIdx.x;
-  const int stm = sup / g.tiles_n, tn = sup - stm * g.tiles_n;
+  const int stm = __builtin_amdgcn_readfirstlane(sup / g.tiles_n), tn = sup - stm * g.tiles_n;
   const int per = g.pk / (int)gridDim.y;  // slices of this workgroup
   for (int q = 0; q < per; ++q) {
     const int split = (int)blockIdx.y * per + q;
@@ -629,9 +724,13 @@ hipError_t launch_dl(const Plan& p, const GemmArgs& g, hipStream_t st, bool obf)
   return hipGetLastError();
 }
 
+// Workgroups per CU for the planner: the device's figure, but no more than
+// the configuration is built for, which is what its costs were fitted with
+// (28921 x 20011 x 59: a 128 x 128 x 32 tile priced at three per CU was taken
+// at 320 us where the 64 x 512 one runs in 298).
 template <int BM, int BN, int BK, int S>
 int occ_dl() {
-  int o = 1 << 20;
+  int o = Dl<BM, BN, BK, S>::WPE;
   const void* ks[6] = {reinterpret_cast<const void*>(k_dl<BM, BN, BK, S, DL_F32>),
                        reinterpret_cast<const void*>(k_dl<BM, BN, BK, S, DL_BF16>),
                        reinterpret_cast<const void*>(k_dl<BM, BN, BK, S, DL_PARTIAL>), nullptr, nullptr, nullptr};
