@@ -22,12 +22,15 @@ ARCH = "gfx950"
 SOURCES = ["kernels.hip", "kernels_dl.hip", "kernels_tall.hip", "planner.cpp", "adaptcore.cpp", "noalloc.hip"]
 # compilation units: (source, object name, extra flags); the kernels are
 # compiled once per input format (bf16, and fp16 in namespace ac::f16)
-UNITS = [("kernels.hip", "kernels.hip.o", []), ("kernels.hip", "kernels_f16.hip.o", ["-DAC_INPUT_F16=1"]),
-         ("kernels_dl.hip", "kernels_dl.hip.o", []), ("kernels_dl.hip", "kernels_dl_f16.hip.o", ["-DAC_INPUT_F16=1"]),
-         ("kernels_tall.hip", "kernels_tall.hip.o", []),
-         ("kernels_tall.hip", "kernels_tall_f16.hip.o", ["-DAC_INPUT_F16=1"]),
-         ("planner.cpp", "planner.cpp.o", []), ("adaptcore.cpp", "adaptcore.cpp.o", []),
-         ("noalloc.hip", "noalloc.hip.o", [])]
+F16 = ["-DAC_INPUT_F16=1"]
+DL_PARTS = 7  # kernels_dl.hip: the dispatch, then six groups of configurations
+UNITS = [("kernels.hip", "kernels.hip.o", []), ("kernels.hip", "kernels_f16.hip.o", F16)]
+for _p in range(DL_PARTS):
+    UNITS += [("kernels_dl.hip", "kernels_dl_%d.hip.o" % _p, ["-DAC_DL_PART=%d" % _p]),
+              ("kernels_dl.hip", "kernels_dl_%d_f16.hip.o" % _p, ["-DAC_DL_PART=%d" % _p] + F16)]
+UNITS += [("kernels_tall.hip", "kernels_tall.hip.o", []), ("kernels_tall.hip", "kernels_tall_f16.hip.o", F16),
+          ("planner.cpp", "planner.cpp.o", []), ("adaptcore.cpp", "adaptcore.cpp.o", []),
+          ("noalloc.hip", "noalloc.hip.o", [])]
 HEADERS = ["kernel_args.h", "variants.h", "planner.h", "registry.h", "noalloc.h", "device_common.h"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH, "-Wall", "-Wno-unused-function",
@@ -76,7 +79,7 @@ def build(verbose=False, incremental=False):
     than its source or a header) and links the library."""
     os.makedirs(BUILD, exist_ok=True)
     todo = [u for u in UNITS if not incremental or _obj_stale(u)]
-    with cf.ThreadPoolExecutor(max(1, len(todo))) as ex:
+    with cf.ThreadPoolExecutor(max(1, min(len(todo), os.cpu_count() or 8))) as ex:
         results = list(ex.map(_compile, todo))
     for _, err in results:
         if verbose and err.strip():

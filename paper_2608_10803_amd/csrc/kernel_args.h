@@ -59,6 +59,10 @@ struct GemmArgs {
   // copy). K is then the k the loop runs over: rounded up to 8 when A is a
   // zero-padded copy. Other kernels ignore both.
   int64_t kB, nB;
+  // Direct-to-LDS kernels: operands read in place column-major (bit 0: A,
+  // stored as K rows of M; bit 1: B, stored as N rows of K), lda and ldb then
+  // those rows' pitches. Other kernels ignore it (0).
+  int lay;
 };
 
 // Arguments of the grouped kernel. With counts: group g owns rows

@@ -42,6 +42,9 @@
 #ifndef AC_INPUT_F16
 #define AC_INPUT_F16 0
 #endif
+#ifndef AC_DL_PART
+#define AC_DL_PART 0
+#endif
 
 namespace ac {
 #if AC_INPUT_F16
@@ -58,7 +61,27 @@ typedef __attribute__((address_space(3))) tr16x4 lds_tr16x4;
 
 enum DlOut : int { DL_F32 = 0, DL_BF16 = 1, DL_PARTIAL = 2 };
 
-template <int BM, int BN, int BK_, int S_>
+// One operand's tile of a stage: EXT rows of A (or columns of B) by BK of k.
+// KC: k runs along the stored rows (a row-major A, a column-major B): EXT rows
+// of BK, MFMA fragments read with ds_read_b128. Otherwise the extent does (a
+// row-major B, a column-major A): BK rows of EXT, fragments read with the
+// transpose read. Either way 16-byte chunks swizzled within their row, and a
+// lane gets the same 8 consecutive k of the same row or column.
+template <int EXT_, int BK, bool KC_>
+struct DlOp {
+  static constexpr int EXT = EXT_;
+  static constexpr bool KC = KC_;
+  static constexpr int ROW = (KC ? BK : EXT) * 2;  // bytes of a stored row
+  static constexpr int BYTES = EXT * BK * 2;
+  static constexpr int LPR = ROW / 16;     // 16-byte chunks of a row
+  static constexpr int RPI = 64 / LPR;     // rows per wave-wide load
+  static constexpr int NI = BYTES / 4096;  // wave-wide loads per wave and stage
+  static constexpr int READS = KC ? 1 : 2; // LDS reads of a fragment
+  static_assert(KC || EXT >= 128, "the k-row swizzle spans 16 chunks");
+};
+
+// LAY: bit 0, A column-major in memory; bit 1, B column-major.
+template <int BM, int BN, int BK_, int S_, int LAY = 0>
 struct Dl {
   static constexpr int BN_ = BN, BK = BK_, S = S_, NT = 256;
   // waves: 2 x 2 quadrants, or (tiles of at most 64 rows: the decode-style
@@ -66,13 +89,11 @@ struct Dl {
   static constexpr int WM = BM >= 128 ? 2 : 1, WN = 4 / WM;
   static constexpr int WTM = BM / WM, WTN = BN / WN;  // a wave's part of the tile
   static constexpr int TM = WTM / 32, TN = WTN / 32;
-  static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BK * BN * 2;
-  static constexpr int A_LPR = BK / 8;        // 16-byte chunks of an A row
-  static constexpr int A_RPI = 64 / A_LPR;    // A rows per wave-wide load
-  static constexpr int B_LPR = BN / 8;        // 16-byte chunks of a B row
-  static constexpr int B_RPI = 64 / B_LPR;    // B rows per wave-wide load
-  static constexpr int NIA = A_BYTES / 4096;  // wave-wide loads per wave and A stage
-  static constexpr int NIB = B_BYTES / 4096;
+  typedef DlOp<BM, BK, (LAY & 1) == 0> OA;
+  typedef DlOp<BN, BK, (LAY & 2) != 0> OB;
+  static constexpr int A_BYTES = OA::BYTES, B_BYTES = OB::BYTES;
+  static constexpr int A_LPR = OA::LPR, A_RPI = OA::RPI, B_LPR = OB::LPR, B_RPI = OB::RPI;
+  static constexpr int NIA = OA::NI, NIB = OB::NI;
   static constexpr int LOADS = NIA + NIB;
   static constexpr int CT_LD = WTN + 4;       // padded row of the bf16 output slab
   // workgroups per CU the configuration is built for: two when two fit the
@@ -113,43 +134,57 @@ __device__ __forceinline__ void stage_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// Per-tile addressing of a workgroup's loads: the byte offset of every
-// 16-byte chunk this lane loads (OOB_OFF for rows past M and columns past
-// N), and the k of that chunk within the block for the K tail.
+// Addressing of a workgroup's loads of one operand: the byte offset of every
+// 16-byte chunk this lane loads (OOB_OFF for rows and columns outside the
+// matrix), and the k of that chunk within the block for the K tail.
+template <class O, int BK>
+struct DlOpTile {
+  const char* base;       // the tile's first row (column) at k = 0
+  int64_t kstep;          // bytes from one k to the next
+  int32_t off[O::NI];
+  int32_t k[O::KC ? O::NI : 1];  // KC: k of each chunk; else the k-row of the first one
+
+  // p: the operand, ld its row pitch, e0 the tile's first row or column, left
+  // how many of them the matrix has from there on
+  __device__ __forceinline__ void init(const uint16_t* p, int64_t ld, int64_t e0, int64_t left, int w) {
+    const int lane = threadIdx.x & 63;
+    base = reinterpret_cast<const char*>(p + e0 * (O::KC ? ld : 1));
+    kstep = 2 * (O::KC ? 1 : ld);
+    if constexpr (!O::KC) k[0] = lane / O::LPR;
+#pragma unroll
+    for (int q = 0; q < O::NI; ++q) {
+      const int row = (w * O::NI + q) * O::RPI + lane / O::LPR;  // stored row of the tile
+      const int c = (lane % O::LPR) ^ (O::KC ? swz_a<BK>(row) : swz_b(row));  // the chunk this slot holds
+      off[q] = (O::KC ? row : c * 8) < left ? (int32_t)(row * ld * 2) + c * 16 : OOB_OFF;
+      if constexpr (O::KC) k[q] = c * 8;
+    }
+  }
+  // load q (a compile-time index) of wave w into a stage: cur = the block's
+  // first k, rem = k left from there
+  __device__ __forceinline__ void issue(const char* cur, int rem, char* stage, int w, int q) const {
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(cur), (short)0,
+                                                                       (int)0x7FFFFFF0, (int)RSRC_WORD3);
+    const bool in = O::KC ? k[O::KC ? q : 0] < rem : k[0] < rem - (w * O::NI + q) * O::RPI;
+    const int32_t o = in ? off[q] : OOB_OFF;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(stage + (w * O::NI + q) * 1024), 16, o, 0, 0, 0);
+  }
+};
+
 template <class G>
 struct DlTile {
-  const char* a;  // A + m0 * lda
-  const char* b;  // B + n0
-  int64_t ldb2;
-  int64_t K, kB;  // k of the loop (A's columns), rows of B
-  int w;          // wave (uniform)
-  int32_t a_off[G::NIA], b_off[G::NIB];
-  int32_t a_k[G::NIA], b_k0;
+  DlOpTile<typename G::OA, G::BK> a;
+  DlOpTile<typename G::OB, G::BK> b;
+  int64_t K, kA, kB;  // k of the loop; k each operand holds
+  int w;              // wave (uniform)
 
   __device__ __forceinline__ void init(const GemmArgs& g, int64_t m0, int64_t n0) {
-    const int lane = threadIdx.x & 63;
     w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    a = reinterpret_cast<const char*>(g.A + m0 * g.lda);
-    b = reinterpret_cast<const char*>(g.B + n0);
-    ldb2 = g.ldb * 2;
     K = g.K;
-    kB = g.kB;
-    const int64_t rows = g.M - m0, cols = g.nB - n0;
-#pragma unroll
-    for (int q = 0; q < G::NIA; ++q) {
-      const int u = w * G::NIA + q;            // 1024-byte block of the stage: A_RPI rows
-      const int row = u * G::A_RPI + lane / G::A_LPR;
-      const int c = (lane % G::A_LPR) ^ swz_a<G::BK>(row);  // the chunk this slot holds
-      a_off[q] = row < rows ? (int32_t)(row * g.lda * 2) + c * 16 : OOB_OFF;
-      a_k[q] = c * 8;
-    }
-    b_k0 = lane / G::B_LPR;
-#pragma unroll
-    for (int q = 0; q < G::NIB; ++q) {
-      const int kr = (w * G::NIB + q) * G::B_RPI + b_k0;
-      const int c = (lane % G::B_LPR) ^ swz_b(kr);
-      b_off[q] = c * 8 < cols ? (int32_t)(kr * g.ldb * 2) + c * 16 : OOB_OFF;
-    }
+    // (g.K is rounded up to 8 when A is a zero-padded row-major copy)
+    kA = G::OA::KC ? g.K : g.kB;
+    kB = G::OB::KC ? g.K : g.kB;
+    a.init(g.A, g.lda, m0, g.M - m0, w);
+    b.init(g.B, g.ldb, n0, (G::OB::KC ? g.N : g.nB) - n0, w);
   }
 };
 
@@ -164,35 +199,27 @@ template <class G>
 struct StageLoads {
   const char* pa;  // the block's first k of A's tile, and of B's
   const char* pb;
-  int remA, remB;  // k of A, rows of B from there to the partition's end
+  int remA, remB;  // k of A and of B from there to the partition's end
   char* sA;
   char* sB;
   __device__ __forceinline__ void start(const DlTile<G>& t, int64_t kbeg, int64_t kstop) {
-    pa = t.a + kbeg * 2;
-    pb = t.b + kbeg * t.ldb2;
-    remA = (int)(min(kstop, t.K) - kbeg);
+    pa = t.a.base + kbeg * t.a.kstep;
+    pb = t.b.base + kbeg * t.b.kstep;
+    remA = (int)(min(kstop, t.kA) - kbeg);
     remB = (int)(min(kstop, t.kB) - kbeg);
   }
   __device__ __forceinline__ void next(const DlTile<G>& t) {
-    pa += G::BK * 2;
-    pb += G::BK * t.ldb2;
+    pa += G::BK * t.a.kstep;
+    pb += G::BK * t.b.kstep;
     remA -= G::BK;
     remB -= G::BK;
   }
   // load q of this wave (0 .. NIA + NIB - 1; a compile-time index)
   __device__ __forceinline__ void issue(const DlTile<G>& t, int q) const {
-    if (q < G::NIA) {
-      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(pa), (short)0,
-                                                                         (int)0x7FFFFFF0, (int)RSRC_WORD3);
-      const int32_t off = t.a_k[q] < remA ? t.a_off[q] : OOB_OFF;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(sA + (t.w * G::NIA + q) * 1024), 16, off, 0, 0, 0);
-    } else {
-      const int qb = q - G::NIA;
-      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(pb), (short)0,
-                                                                         (int)0x7FFFFFF0, (int)RSRC_WORD3);
-      const int32_t off = t.b_k0 < remB - (t.w * G::NIB + qb) * G::B_RPI ? t.b_off[qb] : OOB_OFF;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(sB + (t.w * G::NIB + qb) * 1024), 16, off, 0, 0, 0);
-    }
+    if (q < G::NIA)
+      t.a.issue(pa, remA, sA, t.w, q);
+    else
+      t.b.issue(pb, remB, sB, t.w, q - G::NIA);
   }
 };
 
@@ -289,64 +316,76 @@ struct RegLoads {
   }
 };
 
-// Fragments of one k-step (16 k) of a stage: TM A fragments (ds_read_b128
-// of a swizzled row chunk) and TN B fragments (two transpose reads each).
+// Byte offsets of a lane's fragment reads within a stage, computed once. KC:
+// one per k-step (rows are ROW bytes apart, and the swizzle of row 32 i + l32
+// is that of l32); else one per fragment (k-step and half are constant
+// offsets: the swizzle only depends on the k-row mod 4). Opaque to the
+// compiler: it may not take the sums apart into a chain of address steps, at
+// whose end it no longer knows which stage is read and would wait for the
+// loads into all of them.
+template <class O, int BK, int T>
+struct FragAddr {
+  int at[O::KC ? BK / 16 : T];
+  __device__ __forceinline__ void init(int e0) {  // e0: the wave's first row or column in the tile
+    const int lane = threadIdx.x & 63;
+    const int l32 = lane & 31, hi = lane >> 5, i16 = lane & 15, g = lane >> 4;
+    if constexpr (O::KC) {
+#pragma unroll
+      for (int ks = 0; ks < BK / 16; ++ks) {
+        const int ch = 2 * ks + hi;  // 8 consecutive k of the lane's k-group
+        at[ks] = (e0 + l32) * O::ROW + ((ch ^ swz_a<BK>(l32)) << 4);
+        asm("" : "+v"(at[ks]));
+      }
+    } else {
+      // the transpose read of a 16-lane group covers 4 k-rows x 16 columns: lane
+      // i16 addresses k-row i16 >> 2 and columns 4 * (i16 & 3) .. +3 and receives
+      // column i16 of the 4 rows; groups 0 / 1 take columns 0-15 / 16-31 of the
+      // fragment at the lane's k-group 0, groups 2 / 3 the same at k-group 1
+      const int kr0 = 8 * (g >> 1) + (i16 >> 2);
+#pragma unroll
+      for (int j = 0; j < T; ++j) {
+        const int col = e0 + 32 * j + 16 * (g & 1) + (i16 & 3) * 4;
+        at[j] = kr0 * O::ROW + ((col >> 3) ^ swz_b(kr0)) * 16 + (col & 7) * 2;
+        asm("" : "+v"(at[j]));
+      }
+    }
+  }
+  // fragment i of k-step ks (compile-time indices)
+  __device__ __forceinline__ u32x4 read(const char* st, int ks, int i) const {
+    if constexpr (O::KC) {
+      return *reinterpret_cast<const u32x4*>(st + at[ks] + 32 * i * O::ROW);
+    } else {
+      uint32_t v[4];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const tr16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr16x4*)(st + at[i] + (16 * ks + 4 * h) * O::ROW));
+        const uint64_t bits = __builtin_bit_cast(uint64_t, r);
+        v[2 * h] = (uint32_t)bits;
+        v[2 * h + 1] = (uint32_t)(bits >> 32);
+      }
+      return u32x4{v[0], v[1], v[2], v[3]};
+    }
+  }
+};
+
+// Fragments of one k-step (16 k) of a stage.
 template <class G>
 struct Frags {
   u32x4 a[G::TM], b[G::TN];
 };
 
-// Byte offsets of a lane's fragment reads within a stage, computed once: one
-// per k-step for A (its rows are BK * 2 bytes apart, the swizzle of row 32 i +
-// l32 is that of l32), one per column fragment for B (k-step and half are
-// constant offsets: the swizzle only depends on the k-row mod 4).
 template <class G>
-struct FragAddr {
-  int a[G::BK / 16], b[G::TN];
-  __device__ __forceinline__ void init(int wr, int wc) {
-    const int lane = threadIdx.x & 63;
-    const int l32 = lane & 31, hi = lane >> 5, i16 = lane & 15, g = lane >> 4;
-#pragma unroll
-    for (int ks = 0; ks < G::BK / 16; ++ks) {
-      const int ch = 2 * ks + hi;  // 8 consecutive k of the lane's k-group
-      a[ks] = (wr * G::WTM + l32) * (G::BK * 2) + ((ch ^ swz_a<G::BK>(l32)) << 4);
-      // opaque: a sum the compiler may not take apart into a chain of
-      // address steps, at whose end it no longer knows which stage is read
-      // (and would wait for the loads into all of them)
-      asm("" : "+v"(a[ks]));
-    }
-    // the transpose read of a 16-lane group covers 4 k-rows x 16 columns: lane
-    // i16 addresses k-row i16 >> 2 and columns 4 * (i16 & 3) .. +3 and receives
-    // column i16 of the 4 rows; groups 0 / 1 take columns 0-15 / 16-31 of the
-    // fragment at the lane's k-group 0, groups 2 / 3 the same at k-group 1
-    const int kr0 = 8 * (g >> 1) + (i16 >> 2);
-#pragma unroll
-    for (int j = 0; j < G::TN; ++j) {
-      const int col = wc * G::WTN + 32 * j + 16 * (g & 1) + (i16 & 3) * 4;
-      b[j] = kr0 * (G::BN_ * 2) + ((col >> 3) ^ swz_b(kr0)) * 16 + (col & 7) * 2;
-      asm("" : "+v"(b[j]));
-    }
-  }
+struct FragAddrs {
+  FragAddr<typename G::OA, G::BK, G::TM> a;
+  FragAddr<typename G::OB, G::BK, G::TN> b;
 };
 
 template <class G>
-__device__ __forceinline__ void read_frags(const char* sA, const char* sB, int ks, const FragAddr<G>& at, Frags<G>& f) {
+__device__ __forceinline__ void read_frags(const char* sA, const char* sB, int ks, const FragAddrs<G>& at, Frags<G>& f) {
 #pragma unroll
-  for (int i = 0; i < G::TM; ++i)
-    f.a[i] = *reinterpret_cast<const u32x4*>(sA + at.a[ks] + 32 * i * (G::BK * 2));
+  for (int i = 0; i < G::TM; ++i) f.a[i] = at.a.read(sA, ks, i);
 #pragma unroll
-  for (int j = 0; j < G::TN; ++j) {
-    uint32_t v[4];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const tr16x4 r =
-          __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr16x4*)(sB + at.b[j] + (16 * ks + 4 * h) * (G::BN_ * 2)));
-      const uint64_t bits = __builtin_bit_cast(uint64_t, r);
-      v[2 * h] = (uint32_t)bits;
-      v[2 * h + 1] = (uint32_t)(bits >> 32);
-    }
-    f.b[j] = u32x4{v[0], v[1], v[2], v[3]};
-  }
+  for (int j = 0; j < G::TN; ++j) f.b[j] = at.b.read(sB, ks, j);
 }
 
 // What runs under the NMF MFMAs of one k-step: RD LDS reads (the next step's
@@ -375,9 +414,9 @@ __device__ __forceinline__ void mfma_step(const Frags<G>& f, f32x16 (&acc)[G::TM
 
 // One output tile (tile coordinates tm, tn) over K partition `split` of the
 // plan's kper-block partitions.
-template <int BM, int BN, int BK, int S, int OUT, bool RG>
+template <int BM, int BN, int BK, int S, int OUT, bool RG, int LAY = 0>
 __device__ __forceinline__ void dl_tile(const GemmArgs& g, int tm, int tn, int split) {
-  typedef Dl<BM, BN, BK, S> G;
+  typedef Dl<BM, BN, BK, S, LAY> G;
   typedef typename std::conditional<RG, DlTileU<G>, DlTile<G>>::type Tile;
   typedef typename std::conditional<RG, RegLoads<G>, StageLoads<G>>::type Loads;
   __shared__ __attribute__((aligned(1024))) char lA0[G::A_BYTES];
@@ -436,7 +475,8 @@ __device__ __forceinline__ void dl_tile(const GemmArgs& g, int tm, int tn, int s
   // start of each block, after its barrier, the four waves' 32 KB of first
   // fragments (256 clocks of LDS time) were exposed per 2060 clocks of MFMAs
   // on the 256 x 256 x 64 tile.
-  constexpr int KS = G::BK / 16, NMF = G::TM * G::TN, RD = G::TM + 2 * G::TN;
+  constexpr int KS = G::BK / 16, NMF = G::TM * G::TN;
+  constexpr int RD = G::TM * G::OA::READS + G::TN * G::OB::READS;
   // loads of a block per k-step, from the barrier on: with two stages over the
   // first half of a block's MFMAs (they must land within the other half),
   // with more stages over all of them. 8192^3 on the 256 x 256 x 64 tile: all
@@ -444,8 +484,9 @@ __device__ __forceinline__ void dl_tile(const GemmArgs& g, int tm, int tn, int s
   constexpr int LSTEPS = S == 2 ? (KS + 1) / 2 : KS;
   constexpr int LPS = RG ? G::LOADS : (G::LOADS + LSTEPS - 1) / LSTEPS;
   constexpr int REST = G::LOADS - LPS;  // loads left for the next block's k-steps
-  FragAddr<G> fa;
-  fa.init(wr, wc);
+  FragAddrs<G> fa;
+  fa.a.init(wr * G::WTM);
+  fa.b.init(wc * G::WTN);
   Frags<G> f[2];
   Loads nxt;
   if (nk > 0) {
@@ -641,7 +682,7 @@ __device__ __forceinline__ void dl_tile(const GemmArgs& g, int tm, int tn, int s
 
 // a workgroup per output tile (blockIdx.x, in the plan's tile order) and K
 // partition (blockIdx.y)
-template <int BM, int BN, int BK, int S, int OUT, bool RG>
+template <int BM, int BN, int BK, int S, int OUT, bool RG, int LAY = 0>
 __device__ __forceinline__ void dl_kernel(const GemmArgs& g) {
   const int ntiles = g.tiles_m * g.tiles_n;
   int tile = blockIdx.x;
@@ -652,7 +693,7 @@ __device__ __forceinline__ void dl_kernel(const GemmArgs& g) {
   // operand pointers stay there and every load loops over its lanes' pointers
   tm = __builtin_amdgcn_readfirstlane(tm);
   tn = __builtin_amdgcn_readfirstlane(tn);
-  dl_tile<BM, BN, BK, S, OUT, RG>(g, tm, tn, (int)blockIdx.y);
+  dl_tile<BM, BN, BK, S, OUT, RG, LAY>(g, tm, tn, (int)blockIdx.y);
 }
 
 // the kernels: operand tiles loaded straight into LDS (k_dl), or through
@@ -666,6 +707,14 @@ template <int BM, int BN, int BK, int S, int OUT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Dl<BM, BN, BK, S>::WPE, Dl<BM, BN, BK, S>::WPE)))
 void k_dlu(GemmArgs g) {
   dl_kernel<BM, BN, BK, S, OUT, true>(g);
+}
+
+// the same with one operand column-major in memory, read in place (LAY 1: A,
+// LAY 2: B): no transposed copy, the same bits
+template <int BM, int BN, int BK, int S, int OUT, int LAY>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Dl<BM, BN, BK, S>::WPE, Dl<BM, BN, BK, S>::WPE)))
+void k_dlc(GemmArgs g) {
+  dl_kernel<BM, BN, BK, S, OUT, false, LAY>(g);
 }
 
 // Off-chip accumulation (the SingleCoreSplitK and HybridSplitK templates of
@@ -701,9 +750,32 @@ void k_dl_sc(GemmArgs g) {
   }
 }
 
+template <int BM, int BN, int BK, int S, int OUT>
+void start_dl(const GemmArgs& g, dim3 grid, hipStream_t st) {
+  const dim3 block(256);
+  if constexpr ((dl_col(BM, BN, BK, S) & 1) != 0)
+    if (g.lay == 1) {
+      hipLaunchKernelGGL((k_dlc<BM, BN, BK, S, OUT, 1>), grid, block, 0, st, g);
+      return;
+    }
+  if constexpr ((dl_col(BM, BN, BK, S) & 2) != 0)
+    if (g.lay == 2) {
+      hipLaunchKernelGGL((k_dlc<BM, BN, BK, S, OUT, 2>), grid, block, 0, st, g);
+      return;
+    }
+  hipLaunchKernelGGL((k_dl<BM, BN, BK, S, OUT>), grid, block, 0, st, g);
+}
+
+}  // namespace
+
+// The launcher and the occupancy of one configuration. A configuration's
+// kernels are compiled where these are instantiated: the file is compiled
+// once per AC_DL_PART, each part with its configurations, so that the build
+// runs in parallel.
 template <int BM, int BN, int BK, int S>
 hipError_t launch_dl(const Plan& p, const GemmArgs& g, hipStream_t st, bool obf) {
   const dim3 grid(p.grid_x, p.grid_y), block(256);
+  if (g.lay != 0 && (p.unal || g.lay == 3 || (g.lay & ~dl_col(BM, BN, BK, S)) != 0)) return hipErrorInvalidValue;
   if (p.unal) {
     if constexpr (dl_has_unal(BM, BN, BK, S)) {
       if (p.pk > 1)
@@ -715,12 +787,13 @@ hipError_t launch_dl(const Plan& p, const GemmArgs& g, hipStream_t st, bool obf)
     } else {
       return hipErrorInvalidValue;
     }
-  } else if (p.pk > 1)
-    hipLaunchKernelGGL((k_dl<BM, BN, BK, S, DL_PARTIAL>), grid, block, 0, st, g);
-  else if (obf)
-    hipLaunchKernelGGL((k_dl<BM, BN, BK, S, DL_BF16>), grid, block, 0, st, g);
-  else
-    hipLaunchKernelGGL((k_dl<BM, BN, BK, S, DL_F32>), grid, block, 0, st, g);
+  } else if (p.pk > 1) {
+    start_dl<BM, BN, BK, S, DL_PARTIAL>(g, grid, st);
+  } else if (obf) {
+    start_dl<BM, BN, BK, S, DL_BF16>(g, grid, st);
+  } else {
+    start_dl<BM, BN, BK, S, DL_F32>(g, grid, st);
+  }
   return hipGetLastError();
 }
 
@@ -748,6 +821,42 @@ int occ_dl() {
   return o;
 }
 
+#define DL_INST(a, b, c, d)                                                                   \
+  template hipError_t launch_dl<a, b, c, d>(const Plan&, const GemmArgs&, hipStream_t, bool); \
+  template int occ_dl<a, b, c, d>();
+#define DL_EXT(a, b, c, d)                                                                           \
+  extern template hipError_t launch_dl<a, b, c, d>(const Plan&, const GemmArgs&, hipStream_t, bool); \
+  extern template int occ_dl<a, b, c, d>();
+// (a configuration is in one part; the static assertion on DL_CFGS below and
+// the linker hold the parts and the table together)
+#if AC_DL_PART == 1
+DL_INST(256, 256, 64, 2)
+#elif AC_DL_PART == 2
+DL_INST(256, 256, 32, 4)
+DL_INST(256, 256, 32, 5)
+#elif AC_DL_PART == 3
+DL_INST(256, 128, 64, 3)
+DL_INST(128, 256, 64, 3)
+#elif AC_DL_PART == 4
+DL_INST(256, 128, 32, 4)
+DL_INST(128, 256, 32, 4)
+DL_INST(128, 128, 64, 3)
+#elif AC_DL_PART == 5
+DL_INST(256, 128, 32, 2)
+DL_INST(128, 128, 64, 2)
+DL_INST(128, 128, 32, 2)
+#elif AC_DL_PART == 6
+DL_INST(32, 256, 64, 4)
+DL_INST(64, 256, 64, 4)
+DL_INST(32, 128, 64, 4)
+DL_INST(64, 512, 32, 2)
+#else
+DL_EXT(256, 256, 64, 2) DL_EXT(256, 256, 32, 4) DL_EXT(256, 256, 32, 5) DL_EXT(256, 128, 64, 3)
+DL_EXT(128, 256, 64, 3) DL_EXT(256, 128, 32, 4) DL_EXT(128, 256, 32, 4) DL_EXT(128, 128, 64, 3)
+DL_EXT(256, 128, 32, 2) DL_EXT(128, 128, 64, 2) DL_EXT(128, 128, 32, 2) DL_EXT(32, 256, 64, 4)
+DL_EXT(64, 256, 64, 4) DL_EXT(32, 128, 64, 4) DL_EXT(64, 512, 32, 2)
+
+namespace {
 typedef hipError_t (*DlLaunchFn)(const Plan&, const GemmArgs&, hipStream_t, bool);
 typedef int (*DlOccFn)();
 #define DL_CFGS(X) X(256, 256, 64, 2), X(256, 128, 64, 3), X(128, 256, 64, 3), X(128, 128, 64, 3), X(256, 256, 32, 4), \
@@ -799,6 +908,7 @@ hipError_t launch_dl_main(const Plan& p, const GemmArgs& g, hipStream_t st) {
   if (p.family != FAM_DL || p.cfg < 0 || p.cfg >= N_DL_CFG) return hipErrorInvalidValue;
   // the register-load form takes any alignment (K >= 8, N >= 8; two stages)
   if (p.unal ? (!kDlCfg[p.cfg].unal || g.K < 8 || g.N < 8) : !ac::dl_operands_aligned(g)) return hipErrorInvalidValue;
+  if ((g.lay & ~kDlCfg[p.cfg].col) != 0) return hipErrorInvalidValue;
   return kDlFns[p.cfg](p, g, st, dtype_out16(p.s.dtype));
 }
 
@@ -806,16 +916,22 @@ void query_occupancy_dl() {
   for (int i = 0; i < N_DL_CFG; ++i) set_runtime_occupancy(FAM_DL, i, kDlOcc[i]());
 }
 
+#endif  // AC_DL_PART
+
 #if AC_INPUT_F16
 }  // namespace f16
-#else
+#elif AC_DL_PART == 0
 bool dl_a_aligned(const void* A, int64_t lda, int64_t K) {
   return (reinterpret_cast<uintptr_t>(A) & 15) == 0 && (lda & 7) == 0 && (K & 7) == 0 && lda < DL_MAX_LD;
 }
 bool dl_b_aligned(const void* B, int64_t ldb, int64_t nB) {
   return (reinterpret_cast<uintptr_t>(B) & 15) == 0 && (ldb & 7) == 0 && (nB & 7) == 0 && ldb < DL_MAX_LD;
 }
-bool dl_operands_aligned(const GemmArgs& g) { return dl_a_aligned(g.A, g.lda, g.K) && dl_b_aligned(g.B, g.ldb, g.nB); }
+// (an operand read in place column-major: rows of M, or of K)
+bool dl_operands_aligned(const GemmArgs& g) {
+  return ((g.lay & 1) ? dl_b_aligned(g.A, g.lda, g.M) : dl_a_aligned(g.A, g.lda, g.K)) &&
+         ((g.lay & 2) ? dl_a_aligned(g.B, g.ldb, g.K) : dl_b_aligned(g.B, g.ldb, g.nB));
+}
 
 // ---- padding prologue (the Padding module of Table 2)
 // dst (rows x ld_dst, ld_dst = cols rounded up to 8, 16-byte aligned) =

@@ -689,14 +689,31 @@ const int kSplits[] = {2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64, 80,
 void add_prologue(const Shape& s, const adaptcore_hw_t& hw, Plan* p) {
   p->ws_a_off = p->ws_b_off = -1;
   p->t_pro = 0;
+  p->rank = p->predicted;
   if (s.M == 0 || s.N == 0 || s.K == 0) return;
-  auto copy = [&](int64_t rows, int64_t cols, int64_t* off) {
+  double in_place = 0;
+  // `direct`: the main kernel reads this operand without the copy when its
+  // rows are aligned (the copy's workspace stays part of the plan: the
+  // operands of a call decide)
+  auto copy = [&](int64_t rows, int64_t cols, int64_t* off, bool direct = false) {
     *off = (p->ws_bytes + 255) / 256 * 256;
     p->ws_bytes = *off + rows * ldw8(cols) * 2;
-    p->t_pro += hw.t_launch + 4.0 * (double)rows * (double)cols / (hw.hbm_bw * hw.hbm_eta);
+    const double t = hw.t_launch + 4.0 * (double)rows * (double)cols / (hw.hbm_bw * hw.hbm_eta);
+    p->t_pro += t;
+    if (direct) in_place += t;
     p->n_launch += 1;
   };
-  if (s.layouts & AC_LAYOUT_A_COL) copy(s.M, s.K, &p->ws_a_off);
+  // one operand at a time, B first, as the dispatcher does; dimensions that
+  // are no multiple of 8 cannot have aligned rows back to back
+  const int can = p->family == FAM_DL && !p->unal ? kDlCfg[p->cfg].col : 0;
+  const bool b_in = (s.layouts & AC_LAYOUT_B_COL) && (can & 2) && s.K % 8 == 0;
+  const bool a_in = (s.layouts & AC_LAYOUT_A_COL) && (can & 1) && s.M % 8 == 0 && !b_in;
+  // Against the small-M kernel, which also reads B in place, the order counts
+  // the copy up to 4096 x 4096 of B: callers rely on that plan there (9.9 us
+  // direct-to-LDS, 12.3 small-M at M = 4); beyond, the measured order decides
+  // (4 x 4096 x 14336: 24.5 against 29.4 us, 16 x 14336 x 4096: 26.2, 31.3).
+  const bool b_rank = b_in && (s.M > 64 || s.K * s.N > (int64_t)4096 * 4096);
+  if (s.layouts & AC_LAYOUT_A_COL) copy(s.M, s.K, &p->ws_a_off, a_in);
   // the padding prologue of the direct-to-LDS kernels: a row-major operand
   // whose rows are not whole 16-byte chunks is copied zero-padded
   else if ((p->family == FAM_DL || p->family == FAM_DLSC) && !p->unal && (s.K % 8) != 0) copy(s.M, s.K, &p->ws_a_off);
@@ -704,10 +721,11 @@ void add_prologue(const Shape& s, const adaptcore_hw_t& hw, Plan* p) {
   // are runs of k), so only the other families copy B; the tall-skinny
   // kernel reads B's transposed copy (N x K, rows padded to 8) in any case
   if (p->family == FAM_TALL) copy(s.N, s.K, &p->ws_b_off);
-  else if ((s.layouts & AC_LAYOUT_B_COL) && p->family != FAM_SKINNY_M) copy(s.K, s.N, &p->ws_b_off);
+  else if ((s.layouts & AC_LAYOUT_B_COL) && p->family != FAM_SKINNY_M) copy(s.K, s.N, &p->ws_b_off, b_rank);
   else if (!(s.layouts & AC_LAYOUT_B_COL) && (p->family == FAM_DL || p->family == FAM_DLSC) && !p->unal && (s.N % 8) != 0)
     copy(s.K, s.N, &p->ws_b_off);
   p->predicted += p->t_pro;
+  p->rank = p->predicted - in_place;
 }
 
 bool finish(const Ctx& c, Plan* p, const Work& w) {
@@ -1088,7 +1106,7 @@ std::vector<Plan> enumerate(const Shape& s, const adaptcore_hw_t& hw, int* cls_o
   }
   for (Plan& p : sel) p.cls = cls;
   std::stable_sort(sel.begin(), sel.end(), [](const Plan& a, const Plan& b) {
-    if (a.predicted != b.predicted) return a.predicted < b.predicted;
+    if (a.rank != b.rank) return a.rank < b.rank;
     return a.variant_key < b.variant_key;
   });
   for (Plan& p : sel) p.n_candidates = (int)sel.size();

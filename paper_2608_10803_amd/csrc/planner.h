@@ -41,6 +41,9 @@ struct Plan {
   double t_pro = 0;      // its model time, included in `predicted`
   int n_candidates = 0;
   double predicted = 0;
+  // the search's order: `predicted`, less the copy of a column-major operand
+  // that the direct-to-LDS kernel reads in place where its rows are aligned
+  double rank = 0;
   int64_t groups = 0;    // grouped product: groups (s.M is then the row capacity);
                          // strided batch: batch count (s is every batch's shape)
 };

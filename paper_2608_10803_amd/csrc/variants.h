@@ -101,24 +101,32 @@ inline int direct_tile(const DirectCfg& c) { return c.wk == 1 ? 64 : 32; }
 // a plan of the direct-load form runs its register-load form if it has one,
 // else `sibling`, the register-staged tile configuration of the same tiling
 // (-1: none).
+// `col`: column-major operands the configuration also reads in place (bit 0:
+// A, tiles of at least 128 rows; bit 1: B), one at a time.
 struct DlCfg {
-  int bm, bn, bk, stages, sibling, occ, unal;
+  int bm, bn, bk, stages, sibling, occ, unal, col;
 };
-constexpr DlCfg kDlCfg[] = {{256, 256, 64, 2, 0, 1, 0}, {256, 128, 64, 3, 1, 1, 0}, {128, 256, 64, 3, 2, 1, 0},
-                            {128, 128, 64, 3, 3, 1, 0}, {256, 256, 32, 4, 0, 1, 0}, {256, 256, 32, 5, 0, 1, 0},
-                            {256, 128, 32, 4, 1, 1, 0}, {128, 256, 32, 4, 2, 1, 0}, {256, 128, 32, 2, 1, 2, 1},
-                            {128, 128, 64, 2, 3, 2, 1}, {128, 128, 32, 2, 3, 2, 1},
+constexpr DlCfg kDlCfg[] = {{256, 256, 64, 2, 0, 1, 0, 3}, {256, 128, 64, 3, 1, 1, 0, 3}, {128, 256, 64, 3, 2, 1, 0, 3},
+                            {128, 128, 64, 3, 3, 1, 0, 3}, {256, 256, 32, 4, 0, 1, 0, 3}, {256, 256, 32, 5, 0, 1, 0, 3},
+                            {256, 128, 32, 4, 1, 1, 0, 3}, {128, 256, 32, 4, 2, 1, 0, 3}, {256, 128, 32, 2, 1, 2, 1, 3},
+                            {128, 128, 64, 2, 3, 2, 1, 3}, {128, 128, 32, 2, 3, 2, 1, 3},
                             // decode-style (few rows): 4 waves side by side along N, B streamed
                             // through 3-4 stages; no tile kernel has their tiling, so their
                             // register-load form is the fallback for unaligned operands
-                            {32, 256, 64, 4, -1, 1, 1}, {64, 256, 64, 4, -1, 1, 1}, {32, 128, 64, 4, -1, 2, 1},
+                            {32, 256, 64, 4, -1, 1, 1, 2}, {64, 256, 64, 4, -1, 1, 1, 2}, {32, 128, 64, 4, -1, 2, 1, 2},
                             // a wide two-per-CU tile for write-bound shapes: 1 KB row segments of
                             // bf16 C per tile, so fewer lines shared with the neighbouring tiles
-                            {64, 512, 32, 2, -1, 2, 1}};
+                            // (512 rows of a column-major B may lie more than 2^31 bytes apart)
+                            {64, 512, 32, 2, -1, 2, 1, 0}};
 constexpr bool dl_has_unal(int bm, int bn, int bk, int stages) {
   for (const DlCfg& d : kDlCfg)
     if (d.bm == bm && d.bn == bn && d.bk == bk && d.stages == stages) return d.unal != 0;
   return false;
+}
+constexpr int dl_col(int bm, int bn, int bk, int stages) {
+  for (const DlCfg& d : kDlCfg)
+    if (d.bm == bm && d.bn == bn && d.bk == bk && d.stages == stages) return d.col;
+  return 0;
 }
 constexpr int N_DL_CFG = sizeof(kDlCfg) / sizeof(kDlCfg[0]);
 
