@@ -23,7 +23,7 @@ SOURCES = ["kernels.hip", "kernels_dl.hip", "kernels_tall.hip", "planner.cpp", "
 # compilation units: (source, object name, extra flags); the kernels are
 # compiled once per input format (bf16, and fp16 in namespace ac::f16)
 F16 = ["-DAC_INPUT_F16=1"]
-DL_PARTS = 7  # kernels_dl.hip: the dispatch, then six groups of configurations
+DL_PARTS = 8  # kernels_dl.hip: the dispatch, six groups of configurations, the grouped kernels
 UNITS = [("kernels.hip", "kernels.hip.o", []), ("kernels.hip", "kernels_f16.hip.o", F16)]
 for _p in range(DL_PARTS):
     UNITS += [("kernels_dl.hip", "kernels_dl_%d.hip.o" % _p, ["-DAC_DL_PART=%d" % _p]),
@@ -31,7 +31,7 @@ for _p in range(DL_PARTS):
 UNITS += [("kernels_tall.hip", "kernels_tall.hip.o", []), ("kernels_tall.hip", "kernels_tall_f16.hip.o", F16),
           ("planner.cpp", "planner.cpp.o", []), ("adaptcore.cpp", "adaptcore.cpp.o", []),
           ("noalloc.hip", "noalloc.hip.o", [])]
-HEADERS = ["kernel_args.h", "variants.h", "planner.h", "registry.h", "noalloc.h", "device_common.h"]
+HEADERS = ["kernel_args.h", "variants.h", "planner.h", "registry.h", "noalloc.h", "device_common.h", "grouped_map.h"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH, "-Wall", "-Wno-unused-function",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -52,6 +52,7 @@ namespace f16 {
 #endif
 
 #include "device_common.h"
+#include "grouped_map.h"
 
 namespace {
 
@@ -750,6 +751,72 @@ void k_dl_sc(GemmArgs g) {
   }
 }
 
+// The grouped and strided-batch products on the direct-to-LDS tile (one tile
+// of one group per workgroup, no K split): k_grouped's tiles and the same
+// sums, so its bits, on operands whose every group has aligned rows.
+//
+// Tile order of a grouped product (swizzle): the tiles of a group run column
+// panel by column panel, its row tiles one after the other (they share the
+// panel's B), and the XCDs take GRP_CHUNK consecutive tiles in turn. Giving
+// each XCD one contiguous eighth of the tiles, as for a plain product, left
+// some XCDs with the heavy groups, whose tiles share B in the L2, and others
+// with the light ones, each of whose tiles streams a panel of its own from
+// HBM. 8192 rows over 64 groups of unequal load, K 4096, N 1536, 128 x 256
+// tiles: register-staged 290 us, this kernel in that order 233, in chunks of
+// one tile 242, 2: 221, 4: 214, 8: 209, 12: 212.
+constexpr int GRP_CHUNK = 8;
+
+template <int BM, int BN, int BK, int S, int OUT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Dl<BM, BN, BK, S>::WPE, Dl<BM, BN, BK, S>::WPE)))
+void k_grouped_dl(GroupArgs a) {
+  const int tiles_n = a.g.tiles_n;
+  int t = blockIdx.x;
+  int grp = 0, tm = 0, tn = 0;
+  int64_t row0 = 0, rows_g = 0;
+  if (a.counts == nullptr) {
+    // strided batch: the grid is exactly groups x row tiles x column tiles
+    if (a.g.swizzle) t = xcd_remap(t, (int)gridDim.x);
+    const int slot = t / tiles_n;
+    tn = t - slot * tiles_n;
+    grp = slot / a.tiles_per_group;
+    tm = slot - grp * a.tiles_per_group;
+    rows_g = a.rows;
+  } else {
+    GroupChunk<BM> first;
+    first.load(a, 0, 0);
+    if (a.g.swizzle) {
+      // over the tiles that exist: whole rounds of 8 chunks, the rest in order
+      const int n = group_tiles_total<BM>(a, first) * tiles_n;
+      if (t >= n) return;
+      const int whole = n / (8 * GRP_CHUNK) * (8 * GRP_CHUNK);
+      if (t < whole) {
+        const int i = t >> 3;
+        t = (i / GRP_CHUNK) * (8 * GRP_CHUNK) + (t & 7) * GRP_CHUNK + i % GRP_CHUNK;
+      }
+    }
+    const int slot = t / tiles_n;
+    if (!group_of_slot<BM>(a, first, slot, grp, row0, rows_g, tm)) return;
+    // the group's tiles start at its first slot's
+    const int in = t - (slot - tm) * tiles_n, rt = (int)((rows_g + BM - 1) / BM);
+    tn = in / rt;
+    tm = in - tn * rt;
+  }
+  // the same values in every lane: scalar for the address bases
+  grp = __builtin_amdgcn_readfirstlane(grp);
+  tm = __builtin_amdgcn_readfirstlane(tm);
+  tn = __builtin_amdgcn_readfirstlane(tn);
+  row0 = uniform64(row0);
+  rows_g = uniform64(rows_g);
+
+  GemmArgs g = a.g;
+  g.A += row0 * g.lda + (int64_t)grp * a.stride_a;
+  g.B += (int64_t)grp * a.stride_b;
+  g.C = static_cast<char*>(g.C) + (row0 * g.ldc + (int64_t)grp * a.stride_c) * (OUT == DL_BF16 ? 2 : 4);
+  if (g.epi && g.bias != nullptr) g.bias += (int64_t)grp * a.stride_bias;
+  g.M = rows_g;
+  dl_tile<BM, BN, BK, S, OUT, false>(g, tm, tn, 0);
+}
+
 template <int BM, int BN, int BK, int S, int OUT>
 void start_dl(const GemmArgs& g, dim3 grid, hipStream_t st) {
   const dim3 block(256);
@@ -821,6 +888,17 @@ int occ_dl() {
   return o;
 }
 
+template <int BM, int BN, int BK, int S>
+hipError_t launch_grouped_dl(const Plan& p, const GroupArgs& a, hipStream_t st, bool obf) {
+  const dim3 grid(p.grid_x), block(256);
+  if (obf)
+    hipLaunchKernelGGL((k_grouped_dl<BM, BN, BK, S, DL_BF16>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((k_grouped_dl<BM, BN, BK, S, DL_F32>), grid, block, 0, st, a);
+  return hipGetLastError();
+}
+#define GDL_INST(a, b, c, d) template hipError_t launch_grouped_dl<a, b, c, d>(const Plan&, const GroupArgs&, hipStream_t, bool);
+#define GDL_EXT(a, b, c, d) extern GDL_INST(a, b, c, d)
 #define DL_INST(a, b, c, d)                                                                   \
   template hipError_t launch_dl<a, b, c, d>(const Plan&, const GemmArgs&, hipStream_t, bool); \
   template int occ_dl<a, b, c, d>();
@@ -850,7 +928,15 @@ DL_INST(32, 256, 64, 4)
 DL_INST(64, 256, 64, 4)
 DL_INST(32, 128, 64, 4)
 DL_INST(64, 512, 32, 2)
+#elif AC_DL_PART == 7
+GDL_INST(256, 128, 64, 3)
+GDL_INST(128, 256, 64, 3)
+GDL_INST(128, 128, 64, 2)
+GDL_INST(128, 128, 64, 3)
+GDL_INST(64, 128, 64, 3)
 #else
+GDL_EXT(256, 128, 64, 3) GDL_EXT(128, 256, 64, 3) GDL_EXT(128, 128, 64, 2) GDL_EXT(128, 128, 64, 3)
+GDL_EXT(64, 128, 64, 3)
 DL_EXT(256, 256, 64, 2) DL_EXT(256, 256, 32, 4) DL_EXT(256, 256, 32, 5) DL_EXT(256, 128, 64, 3)
 DL_EXT(128, 256, 64, 3) DL_EXT(256, 128, 32, 4) DL_EXT(128, 256, 32, 4) DL_EXT(128, 128, 64, 3)
 DL_EXT(256, 128, 32, 2) DL_EXT(128, 128, 64, 2) DL_EXT(128, 128, 32, 2) DL_EXT(32, 256, 64, 4)
@@ -910,6 +996,31 @@ hipError_t launch_dl_main(const Plan& p, const GemmArgs& g, hipStream_t st) {
   if (p.unal ? (!kDlCfg[p.cfg].unal || g.K < 8 || g.N < 8) : !ac::dl_operands_aligned(g)) return hipErrorInvalidValue;
   if ((g.lay & ~kDlCfg[p.cfg].col) != 0) return hipErrorInvalidValue;
   return kDlFns[p.cfg](p, g, st, dtype_out16(p.s.dtype));
+}
+
+// The grouped kernel of a tile configuration in its direct-to-LDS form;
+// hipErrorNotSupported where there is none or the operands are not aligned
+// (the caller then runs the register-staged one, which has the same bits).
+// Every group's operands must be aligned: the first one's, and the strides. A
+// single k-block leaves nothing to pipeline: 96 products of 200 x 200 x 64 run
+// in 6.5 us register-staged (128 x 64 tiles), 6.9 here at best.
+hipError_t launch_grouped_dl_plan(const Plan& p, const GroupArgs& a, hipStream_t st) {
+  const GemmArgs& g = a.g;
+  const bool one = a.groups <= 1;
+  if (g.K < GROUPED_DL_MIN_K || !ac::dl_a_aligned(g.A, g.lda, g.K) || !ac::dl_b_aligned(g.B, g.ldb, g.N) ||
+      (!one && ((a.stride_a & 7) != 0 || (a.stride_b & 7) != 0)))
+    return hipErrorNotSupported;
+  GroupArgs b = a;
+  b.g.kB = g.K;
+  b.g.nB = g.N;
+  const bool obf = dtype_out16(p.s.dtype);
+  const TileCfg& t = kTileCfg[p.cfg];
+  if (t.bm == 256 && t.bn == 128) return launch_grouped_dl<256, 128, 64, 3>(p, b, st, obf);
+  if (t.bm == 128 && t.bn == 256) return launch_grouped_dl<128, 256, 64, 3>(p, b, st, obf);
+  if (t.bm == 128 && t.bn == 128 && t.depth == 1) return launch_grouped_dl<128, 128, 64, 2>(p, b, st, obf);
+  if (t.bm == 128 && t.bn == 128) return launch_grouped_dl<128, 128, 64, 3>(p, b, st, obf);
+  if (t.bm == 64 && t.bn == 128) return launch_grouped_dl<64, 128, 64, 3>(p, b, st, obf);
+  return hipErrorNotSupported;
 }
 
 void query_occupancy_dl() {

@@ -728,6 +728,11 @@ void add_prologue(const Shape& s, const adaptcore_hw_t& hw, Plan* p) {
   p->rank = p->predicted - in_place;
 }
 
+// Direct-to-LDS configuration whose costs price a grouped tile configuration
+// (the same tile and stages; the 64 x 128 one takes the 32 x 128 decode
+// tile's, the nearest two-per-CU one that was timed): -1, none.
+constexpr int kGroupedDl[N_TILE_CFG] = {-1, 1, 2, 9, -1, 13, -1, -1, 3, -1, -1};
+
 bool finish(const Ctx& c, Plan* p, const Work& w) {
   p->s = c.s;
   p->predicted = model_time(c.s, w, c.hw, c.compulsory);
@@ -735,6 +740,21 @@ bool finish(const Ctx& c, Plan* p, const Work& w) {
                    ((uint64_t)(p->unal & 1) << 13);
   add_prologue(c.s, c.hw, p);
   if (p->ws_bytes > ((int64_t)2 << 30)) return false;  // cap of the workspace: partials and operand copies
+  return true;
+}
+
+// Work of one group's product on the grouped kernels. With K and N multiples
+// of 8 the direct-to-LDS kernel of the same tiling runs where there is one
+// (aligned operands), so its costs apply.
+bool group_work(const Ctx& c, int cfg, int swizzle, Plan* one, Work* w) {
+  if (!build_tile(c, cfg, 1, swizzle, one, w)) return false;
+  const int d = kGroupedDl[cfg];
+  if (d < 0 || c.s.K < GROUPED_DL_MIN_K || c.s.K % 8 != 0 || c.s.N % 8 != 0) return true;
+  const DlCfg& t = kDlCfg[d];
+  w->idx = IDX_DL + d;
+  w->occ = occupancy(FAM_DL, d);
+  w->prefetch = (double)(t.stages - 1) * t.bk / TILE_BK;
+  w->unaligned = false;
   return true;
 }
 
@@ -780,7 +800,7 @@ bool build_grouped(const Shape& s, int64_t groups, const adaptcore_hw_t& hw, int
   const Ctx c{sg, hw, compulsory, out_bytes(s.dtype), unaligned};
   Plan one;
   Work w;
-  if (!build_tile(c, cfg, 1, swizzle, &one, &w)) return false;
+  if (!group_work(c, cfg, swizzle, &one, &w)) return false;
   w.units *= ne;
   w.total_read *= (double)ne;
   w.total_write *= (double)ne;
@@ -1201,7 +1221,7 @@ bool build_batched(const Shape& s, int64_t batch, const adaptcore_hw_t& hw, int 
   const Ctx c{s, hw, compulsory, out_bytes(s.dtype), unaligned};
   Plan one;
   Work w;
-  if (!build_tile(c, cfg, 1, swizzle, &one, &w)) return false;
+  if (!group_work(c, cfg, swizzle, &one, &w)) return false;
   w.units *= batch;
   w.total_read *= (double)batch;
   w.total_write *= (double)batch;

@@ -31,6 +31,10 @@ inline int tile_lds_bytes(const TileCfg& t) { return 2 * (t.bm + t.bn) * TILE_BK
 constexpr bool kGroupedCfg[] = {false, true, true, true, true, true, true, false, true, false, false};
 static_assert(sizeof(kGroupedCfg) / sizeof(kGroupedCfg[0]) == N_TILE_CFG, "grouped configurations");
 
+// Grouped and batched products of at least this K (two k-blocks) run on the
+// direct-to-LDS tile where their operands are aligned.
+constexpr int64_t GROUPED_DL_MIN_K = TILE_BK + 1;
+
 // Tile configurations that also have a persistent kernel (one k-block of
 // global loads ahead, carried across tiles): the depth-1 configurations.
 constexpr bool kPersistCfg[] = {true, true, false, true, true, true, false, false, false, false, false};

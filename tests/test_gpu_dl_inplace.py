@@ -1,0 +1,160 @@
+"""GPU parity of the direct-to-LDS kernels' in-place column-major operands and
+grouped form.
+
+A column-major operand with aligned rows is loaded in place: every dl
+configuration of shapes at the edges of tiles, k-blocks and stages runs on
+it, is checked against the fp64 oracle and, bit for bit, against the same
+configuration on operands stored one element further on, which takes the
+transposing copy (the same fragments in the same k order). Grouped and
+batched products with aligned operands run the direct-to-LDS tile; one
+element further on they run the register-staged tile of the same plan: the
+same bits again.
+"""
+import numpy as np
+import pytest
+
+import paper_2608_10803_amd as ac
+from oracle import addmm_ref, grouped_ref, layout_ref
+from workloads import gen
+
+from gpu_util import Out, all_candidates, check, fmt_of, forced_plan, run, run_addmm, to_device, tol, torch
+from oracle import gemm_ref
+
+pytestmark = pytest.mark.gpu
+
+F32, BF16, F16F16 = ac.AC_BF16_F32OUT, ac.AC_BF16_BF16OUT, ac.AC_F16_F16OUT
+
+
+@pytest.fixture(scope="module", autouse=True)
+def device():
+    torch()
+    ac.adaptcore_init()
+    yield
+
+
+def stored(M, N, K, layouts, dtype, seed, pad):
+    """A and B as stored, every stored row `pad` elements longer than its
+    matrix (other values there)."""
+    dist = "uniform_f16" if fmt_of(dtype) == "fp16" else "uniform"
+    A, B = gen.operands(M, N, K, seed=seed, dist=dist)
+    mk = gen.uniform_f16 if dist == "uniform_f16" else gen.uniform_bf16
+    out = []
+    for m, i in ((A.T if layouts & 1 else A, 3), (B.T if layouts & 2 else B, 4)):
+        s = mk(m.shape[0], m.shape[1] + pad, (seed, i), -9.0, 9.0)
+        s[:, :m.shape[1]] = m
+        out.append(s)
+    return out[0], out[0].shape[1], out[1], out[1].shape[1]
+
+
+# (M, N, K, layouts): the operand in place has whole 16-byte chunks (M, or K, a
+# multiple of 8); the other dimensions are odd, K one block and less, just
+# over a block, a whole and a partial group of stages
+SHAPES = [(264, 77, 45, 1), (136, 261, 130, 1), (8, 130, 8, 1), (520, 513, 321, 1),
+          (37, 261, 72, 2), (300, 515, 264, 2), (130, 129, 8, 2), (65, 257, 1032, 2), (5, 300, 520, 2),
+          (136, 270, 200, 3)]
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16, F16F16], ids=["f32", "bf16", "f16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_column_major_in_place(shape, dtype):
+    M, N, K, layouts = shape
+    sa, lda, sb, ldb = stored(M, N, K, layouts, dtype, seed=M + N + K, pad=0 if K == 72 else 8)
+    ref = layout_ref.gemm_layout(sa, sb, M, N, K, lda, ldb, layouts, fmt=fmt_of(dtype))
+    cands = [c for c in all_candidates(M, N, K, dtype, layouts) if c["family_name"] == "dl"]
+    assert cands
+    for c in cands:
+        plan = forced_plan(M, N, K, dtype, c["variant_key"], layouts)
+        vals, ok = run(plan, sa, sb, M, N, K, dtype, lda=lda, ldb=ldb)
+        check(vals, ok, None, None, dtype, ref=ref, label="%s %s" % (shape, c))
+        v2, ok2 = run(plan, sa, sb, M, N, K, dtype, lda=lda, ldb=ldb, a_off=layouts & 1, b_off=layouts >> 1)
+        assert ok2 and np.array_equal(vals.view(np.uint64), v2.view(np.uint64)), (shape, c)
+
+
+def test_addmm_column_major_in_place():
+    M, N, K = 40, 264, 328
+    bias = gen.uniform_f32(1, N, 9).reshape(-1)
+    old = gen.uniform_f32(M, N, 10)
+    sa, lda, sb, ldb = stored(M, N, K, 2, F32, seed=3, pad=0)
+    A, B = sa, np.ascontiguousarray(sb.T)
+    ref = addmm_ref.addmm(A, B, old, -1.5, 0.75, bias)
+    for c in all_candidates(M, N, K, F32, 2):
+        if c["family_name"] != "dl":
+            continue
+        plan = forced_plan(M, N, K, F32, c["variant_key"], 2)
+        vals, ok = run_addmm(plan, sa, sb, M, N, K, F32, old, -1.5, 0.75, bias, lda=lda, ldb=ldb)
+        check(vals, ok, None, None, F32, ref=ref, label=str(c))
+
+
+def grouped(plan, counts, A, B, rows, G, N, K, dtype, a_off, alpha=None, bias=None):
+    t = torch()
+    Ad, a = to_device(A, K, a_off)
+    Bd = t.from_numpy(B.view(np.int16)).to("cuda")
+    cnt = t.from_numpy(np.asarray(counts, np.int32)).to("cuda")
+    out = Out(rows, N, N, dtype)
+    if alpha is None:
+        ac.adaptcore_grouped_matmul(plan, cnt.data_ptr(), a, K, Bd.data_ptr(), N, K * N, out.addr, N, 0)
+    else:
+        bd = t.from_numpy(bias).to("cuda")
+        ac.adaptcore_grouped_addmm(plan, cnt.data_ptr(), a, K, Bd.data_ptr(), N, K * N, out.addr, N, alpha, 0.0,
+                                   bd.data_ptr(), N, 0)
+    t.cuda.synchronize()
+    return out.read()
+
+
+# more and fewer tiles than a round of the tile order (8 XCDs x 8 tiles), row
+# tiles with remainders, empty groups, rows no group covers, more than 64 groups
+GROUPS = [([100, 0, 37, 250, 1, 0, 129, 64, 50], 700, 296, 200), ([1] * 9, 9, 8, 72),
+          ([300, 0, 5], 305, 1304, 136), (list(range(70)), 2500, 136, 264)]
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("case", GROUPS, ids=lambda c: "x".join(map(str, (len(c[0]),) + c[1:])))
+def test_grouped_direct_to_lds(case, dtype):
+    counts, rows, N, K = case
+    G = len(counts)
+    A = gen.uniform_bf16(rows, K, 5)
+    B = np.concatenate([gen.uniform_bf16(K, N, 6 + g).reshape(-1) for g in range(G)])
+    C_ref, D, cov = grouped_ref.grouped_gemm(A, B, np.asarray(counts, np.int32), rows, N, K, K, N, K * N)
+    for cfg in range(11):
+        for sw in (0, 1):
+            key = ac.AC_FAMILY_GROUPED | (cfg << 4) | (sw << 12) | (1 << 16) | (dtype << 48)
+            try:
+                plan = ac.adaptcore_grouped_plan_variant(rows, G, N, K, dtype, 0, key)
+            except ac.AdaptCoreError:
+                continue
+            vals, ok = grouped(plan, counts, A, B, rows, G, N, K, dtype, 0)
+            assert ok and gemm_ref.err_metric(vals[cov], C_ref[cov], D[cov]) <= tol(dtype), (cfg, sw)
+            v2, ok2 = grouped(plan, counts, A, B, rows, G, N, K, dtype, 1)
+            assert ok2 and np.array_equal(vals.view(np.uint64), v2.view(np.uint64)), (cfg, sw)
+            bias = gen.uniform_f32(G, N, 8).reshape(-1)
+            v3, ok3 = grouped(plan, counts, A, B, rows, G, N, K, dtype, 0, -2.0, bias)
+            v4, ok4 = grouped(plan, counts, A, B, rows, G, N, K, dtype, 1, -2.0, bias)
+            assert ok3 and ok4 and np.array_equal(v3.view(np.uint64), v4.view(np.uint64)), (cfg, sw)
+
+
+@pytest.mark.parametrize("shape", [(5, 70, 304, 200), (3, 300, 136, 72), (9, 1, 8, 264), (2, 129, 520, 128)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_batched_direct_to_lds(shape):
+    batch, M, N, K = shape
+    t = torch()
+    A = gen.uniform_bf16(batch * M, K, 1)
+    B = gen.uniform_bf16(batch * K, N, 2)
+    Bd = t.from_numpy(B.view(np.int16)).to("cuda")
+    for cfg in range(11):
+        for sw in (0, 1):
+            key = ac.AC_FAMILY_BATCHED | (cfg << 4) | (sw << 12) | (1 << 16) | (BF16 << 48)
+            try:
+                plan = ac.adaptcore_batched_plan_variant(batch, M, N, K, BF16, 0, key)
+            except ac.AdaptCoreError:
+                continue
+            got = []
+            for off in (0, 1):
+                Ad, a = to_device(A, K, off)
+                out = Out(batch * M, N, N, BF16)
+                ac.adaptcore_batched_matmul(plan, a, K, M * K, Bd.data_ptr(), N, K * N, out.addr, N, M * N, 0)
+                t.cuda.synchronize()
+                got.append(out.read())
+            assert got[0][1] and got[1][1] and np.array_equal(got[0][0].view(np.uint64), got[1][0].view(np.uint64))
+            for b in range(batch):
+                C_ref, D = gemm_ref.gemm(A[b * M:(b + 1) * M], B[b * K:(b + 1) * K])
+                assert gemm_ref.err_metric(got[0][0][b * M:(b + 1) * M], C_ref, D) <= tol(BF16), (cfg, sw, b)
