@@ -308,6 +308,12 @@ adaptcore_status adaptcore_matmul(const adaptcore_plan_t* plan, const void* A, i
 adaptcore_status adaptcore_matmul_noalloc(const adaptcore_plan_t* plan, const void* A, int64_t lda, const void* B,
                                           int64_t ldb, void* C, int64_t ldc, void* stream);
 
+/* adaptcore_plan (the calling thread's override included) and adaptcore_matmul
+ * in one call, for callers that meet a new shape with every call. */
+adaptcore_status adaptcore_matmul_shape(int64_t M, int64_t N, int64_t K, int32_t dtype, uint32_t layouts,
+                                        const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
+                                        void* stream);
+
 /* Size in bytes of the per-GPU array used by adaptcore_matmul_noalloc. */
 int64_t adaptcore_noalloc_scratch_bytes(void);
 

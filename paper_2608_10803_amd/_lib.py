@@ -139,6 +139,8 @@ def lib():
         L.adaptcore_get_override.restype = u64
         L.adaptcore_matmul.argtypes = [p, p, i64, p, i64, p, i64, p]
         L.adaptcore_matmul.restype = i32
+        L.adaptcore_matmul_shape.argtypes = [i64, i64, i64, i32, u32, p, i64, p, i64, p, i64, p]
+        L.adaptcore_matmul_shape.restype = i32
         L.adaptcore_matmul_noalloc.argtypes = [p, p, i64, p, i64, p, i64, p]
         L.adaptcore_matmul_noalloc.restype = i32
         L.adaptcore_noalloc_scratch_bytes.argtypes = []
@@ -245,6 +247,11 @@ def adaptcore_get_override():
 def adaptcore_matmul(plan, A, lda, B, ldb, C, ldc, stream=0):
     """C = A * B on `stream`; A, B, C are device addresses (ints)."""
     return _check(lib().adaptcore_matmul(plan, A, lda, B, ldb, C, ldc, stream))
+
+
+def adaptcore_matmul_shape(M, N, K, dtype, layouts, A, lda, B, ldb, C, ldc, stream=0):
+    """adaptcore_plan and adaptcore_matmul in one call."""
+    return _check(lib().adaptcore_matmul_shape(M, N, K, dtype, layouts, A, lda, B, ldb, C, ldc, stream))
 
 
 def adaptcore_matmul_noalloc(plan, A, lda, B, ldb, C, ldc, stream=0):
@@ -394,46 +401,69 @@ def adaptcore_schedule(kind, Q, L, t_m, t_p, t_drain):
     return lib().adaptcore_schedule(kind, Q, L, t_m, t_p, t_drain)
 
 
+_torch = None       # the torch module, once a tensor wrapper has run
+_dtype_codes = None  # (A, B, C torch dtypes) -> dtype code
+
+
+def _bind_torch():
+    global _torch, _dtype_codes
+    import torch
+    codes = {}
+    for t, f32, same in ((torch.bfloat16, AC_BF16_F32OUT, AC_BF16_BF16OUT),
+                         (torch.float16, AC_F16_F32OUT, AC_F16_F16OUT)):
+        codes[t, t, torch.float32] = f32
+        codes[t, t, t] = same
+    _dtype_codes, _torch = codes, torch
+
+
+def _current_stream():
+    """Handle of the current device's current stream. (torch.cuda.
+    current_stream() builds a Stream object around it, more than a microsecond
+    of a call that takes eight in all.)"""
+    c = _torch._C
+    try:
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    except AttributeError:
+        return _torch.cuda.current_stream().cuda_stream
+
+
 def _operand(t, rows, cols):
     """(column-major?, leading dimension) of a 2-D operand view: rows
     contiguous (stride(1) == 1) or columns contiguous (stride(0) == 1)."""
-    if t.dim() != 2 or not t.is_cuda:
+    if not t.is_cuda:
         raise ValueError("operands must be 2-D GPU tensors")
-    if cols <= 1 or t.stride(1) == 1:
-        col, ld, need = False, (t.stride(0) if rows > 1 else cols), cols
-    elif rows <= 1 or t.stride(0) == 1:
-        col, ld, need = True, (t.stride(1) if cols > 1 else rows), rows
+    sr, sc = t.stride()
+    if cols <= 1 or sc == 1:
+        col, ld, need = False, (sr if rows > 1 else cols), cols
+    elif rows <= 1 or sr == 1:
+        col, ld, need = True, (sc if cols > 1 else rows), rows
     else:
         raise ValueError("operands must have contiguous rows or contiguous columns")
     if ld < need:
         raise ValueError("overlapping operand view")
-    return col, max(ld, 1)
+    return col, (ld if ld > 1 else 1)
 
 
 def _marshal_tensors(A, B, C):
     """(M, N, K, dtype code, layouts, lda, ldb, ldc) of a tensor product,
     after the checks. A and B may be transposed views (contiguous columns);
     C must have contiguous rows."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     M, K = A.shape
     K2, N = B.shape
-    if K2 != K or tuple(C.shape) != (M, N):
+    if K2 != K or C.shape != (M, N):
         raise ValueError("shape mismatch")
-    if A.dtype != B.dtype or A.dtype not in (torch.bfloat16, torch.float16):
-        raise TypeError("A and B must both be bfloat16 or both float16")
-    f16 = A.dtype == torch.float16
-    if C.dtype == torch.float32:
-        dt = AC_F16_F32OUT if f16 else AC_BF16_F32OUT
-    elif C.dtype == A.dtype:
-        dt = AC_F16_F16OUT if f16 else AC_BF16_BF16OUT
-    else:
-        raise TypeError("C must be float32 or the input type")
+    dt = _dtype_codes.get((A.dtype, B.dtype, C.dtype))
+    if dt is None:
+        dt = _dtype_code(A, B, C)  # says what is wrong
     a_col, lda = _operand(A, M, K)
     b_col, ldb = _operand(B, K, N)
-    if C.dim() != 2 or not C.is_cuda or (N > 1 and C.stride(1) != 1):
+    sr, sc = C.stride()
+    if not C.is_cuda or (N > 1 and sc != 1):
         raise ValueError("C must be a 2-D GPU tensor with contiguous rows")
     layouts = (AC_LAYOUT_A_COL if a_col else 0) | (AC_LAYOUT_B_COL if b_col else 0)
-    return M, N, K, dt, layouts, lda, ldb, max(C.stride(0), N, 1)
+    return M, N, K, dt, layouts, lda, ldb, max(sr, N, 1)
 
 
 def matmul_tensors(A, B, C, stream=None, plan=None):
@@ -443,12 +473,13 @@ def matmul_tensors(A, B, C, stream=None, plan=None):
     torch.float16, C torch.float32 or the input type.
     Marshals pointers and leading dimensions; all arithmetic runs in the
     library's kernels."""
-    import torch
     M, N, K, dt, layouts, lda, ldb, ldc = _marshal_tensors(A, B, C)
+    s = stream if stream is not None else _current_stream()
     if plan is None:
-        plan = adaptcore_plan(M, N, K, dt, layouts)
-    s = stream if stream is not None else torch.cuda.current_stream().cuda_stream
-    adaptcore_matmul(plan, A.data_ptr(), lda, B.data_ptr(), ldb, C.data_ptr(), ldc, s)
+        _check((_lib or lib()).adaptcore_matmul_shape(M, N, K, dt, layouts, A.data_ptr(), lda, B.data_ptr(), ldb,
+                                                      C.data_ptr(), ldc, s))
+    else:
+        adaptcore_matmul(plan, A.data_ptr(), lda, B.data_ptr(), ldb, C.data_ptr(), ldc, s)
     return C
 
 
@@ -456,16 +487,15 @@ def addmm_tensors(A, B, C, alpha=1.0, beta=0.0, bias=None, stream=None, plan=Non
     """C = alpha * A @ B + beta * C + bias in place, for torch tensors laid out
     as in matmul_tensors; bias is None or a contiguous float32 GPU tensor of
     N elements."""
-    import torch
     M, N, K, dt, layouts, lda, ldb, ldc = _marshal_tensors(A, B, C)
     bp = 0
     if bias is not None:
-        if bias.dtype != torch.float32 or bias.numel() != N or not bias.is_cuda or not bias.is_contiguous():
+        if bias.dtype != _torch.float32 or bias.numel() != N or not bias.is_cuda or not bias.is_contiguous():
             raise ValueError("bias must be a contiguous float32 GPU tensor of N elements")
         bp = bias.data_ptr()
     if plan is None:
         plan = adaptcore_plan(M, N, K, dt, layouts)
-    s = stream if stream is not None else torch.cuda.current_stream().cuda_stream
+    s = stream if stream is not None else _current_stream()
     adaptcore_addmm(plan, A.data_ptr(), lda, B.data_ptr(), ldb, C.data_ptr(), ldc, float(alpha), float(beta), bp, s)
     return C
 
@@ -493,29 +523,33 @@ def bmm_tensors(A, B, C, alpha=None, beta=0.0, bias=None, stream=None, plan=None
     broadcast with batch stride 0). With alpha given: C[b] = alpha * A[b] @
     B[b] + beta * C[b] + bias (bias None or N float32 values), in place.
     Marshals pointers, leading dimensions and strides only."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     batch, M, K = A.shape
     batch2, K2, N = B.shape
-    if batch2 != batch or K2 != K or tuple(C.shape) != (batch, M, N):
+    if batch2 != batch or K2 != K or C.shape != (batch, M, N):
         raise ValueError("shape mismatch")
-    dt = _dtype_code(A, B, C)
+    dt = _dtype_codes.get((A.dtype, B.dtype, C.dtype))
+    if dt is None:
+        dt = _dtype_code(A, B, C)
     for t, n in ((A, "A"), (B, "B"), (C, "C")):
         _rows_contiguous(t, n)
-    lda, ldb, ldc = max(A.stride(1), K, 1), max(B.stride(1), N, 1), max(C.stride(1), N, 1)
+    (sa, lda, _), (sb, ldb, _), (sc, ldc, _) = A.stride(), B.stride(), C.stride()
+    lda, ldb, ldc = max(lda, K, 1), max(ldb, N, 1), max(ldc, N, 1)
     if plan is None:
         plan = adaptcore_batched_plan(batch, M, N, K, dt)
-    s = stream if stream is not None else torch.cuda.current_stream().cuda_stream
+    s = stream if stream is not None else _current_stream()
     if alpha is None:
-        adaptcore_batched_matmul(plan, A.data_ptr(), lda, A.stride(0), B.data_ptr(), ldb, B.stride(0), C.data_ptr(),
-                                 ldc, C.stride(0), s)
+        adaptcore_batched_matmul(plan, A.data_ptr(), lda, sa, B.data_ptr(), ldb, sb, C.data_ptr(),
+                                 ldc, sc, s)
     else:
         bp = 0
         if bias is not None:
-            if bias.dtype != torch.float32 or bias.numel() != N or not bias.is_cuda or not bias.is_contiguous():
+            if bias.dtype != _torch.float32 or bias.numel() != N or not bias.is_cuda or not bias.is_contiguous():
                 raise ValueError("bias must be a contiguous float32 GPU tensor of N elements")
             bp = bias.data_ptr()
-        adaptcore_batched_addmm(plan, A.data_ptr(), lda, A.stride(0), B.data_ptr(), ldb, B.stride(0), C.data_ptr(),
-                                ldc, C.stride(0), float(alpha), float(beta), bp, s)
+        adaptcore_batched_addmm(plan, A.data_ptr(), lda, sa, B.data_ptr(), ldb, sb, C.data_ptr(),
+                                ldc, sc, float(alpha), float(beta), bp, s)
     return C
 
 
@@ -525,7 +559,8 @@ def grouped_mm_tensors(A, B, counts, C, stream=None, plan=None):
     by all groups), counts an int32 GPU tensor of `groups` row counts (read by
     the kernel, never by the host), C (rows x N). Contiguous rows required.
     Marshals pointers, leading dimensions and strides only."""
-    import torch
+    if _torch is None:
+        _bind_torch()
     rows, K = A.shape
     if B.dim() == 2:
         groups, stride_b = counts.numel(), 0
@@ -534,16 +569,18 @@ def grouped_mm_tensors(A, B, counts, C, stream=None, plan=None):
     else:
         groups, K2, N = B.shape
         stride_b, ldb = B.stride(0), max(B.stride(1), N, 1)
-    if K2 != K or tuple(C.shape) != (rows, N) or counts.numel() != groups:
+    if K2 != K or C.shape != (rows, N) or counts.numel() != groups:
         raise ValueError("shape mismatch")
-    if counts.dtype != torch.int32 or not counts.is_cuda or not counts.is_contiguous():
+    if counts.dtype != _torch.int32 or not counts.is_cuda or not counts.is_contiguous():
         raise ValueError("counts must be a contiguous int32 GPU tensor")
-    dt = _dtype_code(A, B, C)
+    dt = _dtype_codes.get((A.dtype, B.dtype, C.dtype))
+    if dt is None:
+        dt = _dtype_code(A, B, C)
     for t, n in ((A, "A"), (B, "B"), (C, "C")):
         _rows_contiguous(t, n)
     if plan is None:
         plan = adaptcore_grouped_plan(rows, groups, N, K, dt)
-    s = stream if stream is not None else torch.cuda.current_stream().cuda_stream
+    s = stream if stream is not None else _current_stream()
     adaptcore_grouped_matmul(plan, counts.data_ptr(), A.data_ptr(), max(A.stride(0), K, 1), B.data_ptr(), ldb,
                              stride_b, C.data_ptr(), max(C.stride(0), N, 1), s)
     return C

@@ -557,6 +557,14 @@ adaptcore_status adaptcore_matmul(const adaptcore_plan_t* plan, const void* A, i
   return run_matmul(plan, A, lda, B, ldb, C, ldc, stream, 0, 1.0f, 0.0f, nullptr);
 }
 
+adaptcore_status adaptcore_matmul_shape(int64_t M, int64_t N, int64_t K, int32_t dtype, uint32_t layouts,
+                                        const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
+                                        void* stream) {
+  const adaptcore_plan_t* plan = adaptcore_plan(M, N, K, dtype, layouts);
+  if (!plan) return static_cast<adaptcore_status>(adaptcore_last_status());
+  return run_matmul(plan, A, lda, B, ldb, C, ldc, stream, 0, 1.0f, 0.0f, nullptr);
+}
+
 adaptcore_status adaptcore_matmul_noalloc(const adaptcore_plan_t* plan, const void* A, int64_t lda, const void* B,
                                           int64_t ldb, void* C, int64_t ldc, void* stream) {
   return run_matmul(plan, A, lda, B, ldb, C, ldc, stream, 0, 1.0f, 0.0f, nullptr, true);
