@@ -69,7 +69,10 @@ enum { AC_FP16_F32OUT = AC_F16_F32OUT, AC_FP16_FP16OUT = AC_F16_F16OUT };
  * copy in the plan's workspace by a prologue kernel before the main kernel
  * (the copy prologue of the paper's padding module, priced as T_pro in
  * Eq. 7), except a column-major B under the small-M kernel, which reads it
- * in place. Grouped and batched products take row-major operands only. */
+ * in place, and one column-major operand (B if both are) under the
+ * direct-to-LDS tiles where its stored rows are whole aligned 16-byte chunks:
+ * the plan keeps the copy and its workspace, the operands of a call decide.
+ * Grouped and batched products take row-major operands only. */
 enum { AC_LAYOUT_ROW_ROW = 0, AC_LAYOUT_A_COL = 1, AC_LAYOUT_B_COL = 2, AC_LAYOUT_COL_COL = 3 };
 /* The same bits named per operand (A_ROWMAJOR | B_COLMAJOR, ...). */
 enum { AC_A_ROWMAJOR = 0, AC_A_COLMAJOR = AC_LAYOUT_A_COL, AC_B_ROWMAJOR = 0, AC_B_COLMAJOR = AC_LAYOUT_B_COL };

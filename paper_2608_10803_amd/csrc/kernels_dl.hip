@@ -21,6 +21,9 @@
 // writes 1024 contiguous bytes (lane l to bytes 16l .. 16l+15), so each lane
 // fetches the global chunk that belongs at its slot.
 //
+// (A column-major operand read in place, k_dlc, trades places: a B of N rows
+// of k is tiled and read like A here, an A of K rows of M like B.)
+//
 // k_dl needs row-major operands with 16-byte aligned rows (A and B base
 // addresses 16-byte aligned, lda and ldb multiples of 8 below 2^22) and K, N
 // multiples of 8. A plan for other shapes either copies the operand
