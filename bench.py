@@ -169,7 +169,8 @@ def moe_stream(ac, torch, counts, steps, warmup, grouped):
     if grouped:
         pu = ac.adaptcore_grouped_plan(T, E, F, H, bf)
         pd = ac.adaptcore_grouped_plan(T, E, H, F, bf)
-        kernels = ac.adaptcore_plan_kernels(pu) + ac.adaptcore_plan_kernels(pd)
+        kernels = (ac.adaptcore_call_info(pu, X.data_ptr(), H, Wu.data_ptr(), F, stride_b=H * F)["kernels"] +
+                   ac.adaptcore_call_info(pd, Hb.data_ptr(), F, Wd.data_ptr(), H, stride_b=F * H)["kernels"])
     else:
         ws = 0
         kernels = set()
@@ -559,11 +560,11 @@ def ablation_main(args):
 
 def layouts_main(args):
     """Column-major operands: each shape planned and timed with row-major A
-    and B and with each transposed layout (the prologue copies the
-    column-major operand into the workspace, then the row-major plan runs);
-    the extra time over row-major is the prologue's, reported with the rate
-    at which it moves the copied bytes (read + write). A column-major B under
-    the small-M kernel is read in place (no copy)."""
+    and B and with each transposed layout. A call reads a column-major operand
+    in place where it can, else a prologue copies it into the workspace and
+    the row-major plan runs: the extra time over row-major is then the
+    prologue's, reported with the rate at which it moves the copied bytes
+    (read + write)."""
     import torch
     import paper_2608_10803_amd as ac
     bf = ac.AC_BF16_BF16OUT
@@ -576,14 +577,14 @@ def layouts_main(args):
             t = time_plan(ac, torch, plan, M, N, K, bf)
             if lay == 0:
                 t0 = t
-            names = ac.adaptcore_plan_kernels(plan)
-            b_in_place = any(n.startswith("k_skinny_m_bt<") for n in names)
-            moved = 4 * ((M * K if lay & 1 else 0) + (K * N if lay & 2 and not b_in_place else 0))
+            call = ac.adaptcore_call_info(plan, 4096, M if lay & 1 else K, 4096, K if lay & 2 else N)  # as time_plan's
+            copied = lay & ~call["in_place"]
+            moved = 4 * ((M * K if copied & 1 else 0) + (K * N if copied & 2 else 0))
             r = {"shape": [M, N, K], "layouts": lay, "us": round(t * 1e6, 2), "vs_row_major": round(t / t0, 3),
-                 "predicted_us": round(ac.adaptcore_plan_info(plan)["predicted_s"] * 1e6, 2), "kernels": names}
-            if moved:
+                 "predicted_us": round(call["predicted_s"] * 1e6, 2), "kernels": call["kernels"]}
+            if moved and t > t0:  # (another kernel may make up for the copy)
                 r["prologue_us"] = round((t - t0) * 1e6, 2)
-                r["prologue_gbps"] = round(moved / max(t - t0, 1e-9) / 1e9, 1)
+                r["prologue_gbps"] = round(moved / (t - t0) / 1e9, 1)
             rows.append(r)
             print("layouts", r, file=sys.stderr, flush=True)
     line = {"metric": "time per call by operand layout (prologue copy of column-major operands)", "value": None,

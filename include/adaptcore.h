@@ -136,12 +136,24 @@ typedef struct {
   int32_t grid_x, grid_y; /* launch grid (workgroups of 256 threads) */
   int32_t swizzle;      /* 1 = XCD-aware grouped tile order (ShuffleK analogue) */
   int32_t n_candidates; /* legal candidates the model compared */
-  double predicted_s;   /* model latency of the selected configuration, seconds */
+  double predicted_s;   /* model latency of the selected configuration, seconds, every copy
+                           of an operand that the plan provides for included */
   int64_t workspace_bytes; /* per stream: fp32 partials, then row-major copies of column-major
-                              operands */
+                              operands; enough for any call of the plan (what one call takes:
+                              adaptcore_call_info) */
   int64_t groups;       /* grouped plans: number of groups (M is the row capacity); batched
                            plans: batch count (M, N, K of every batch); else 0 */
 } adaptcore_plan_desc_t;
+
+/* What a call of a plan launches on given operands (adaptcore_call_info). */
+typedef struct {
+  uint64_t variant_key;    /* configuration that runs: the plan's, or its fallback for these operands */
+  uint32_t in_place;       /* AC_LAYOUT_* bits of the column-major operands read where they are */
+  int32_t n_kernels;       /* kernels launched (0: an empty output) */
+  int64_t workspace_bytes; /* workspace the call takes */
+  double predicted_s;      /* the plan's model latency, less the copies the call does not make */
+  char kernels[256];       /* as adaptcore_plan_kernels writes them */
+} adaptcore_call_desc_t;
 
 /* One legal candidate of a shape (adaptcore_candidates). */
 typedef struct {
@@ -459,11 +471,25 @@ adaptcore_status adaptcore_reserve_workspace(void* stream, int64_t bytes);
  * size. AC_ERR_INVALID_VALUE for a null argument. */
 adaptcore_status adaptcore_plan_info(const adaptcore_plan_t* plan, adaptcore_plan_desc_t* out);
 
-/* Writes the kernels one call of the plan launches, in launch order, as
- * "name<template arguments>" separated by ';' (the names a profiler shows,
- * without namespace and parameter list) into buf (capacity len bytes,
- * NUL-terminated). AC_ERR_INVALID_VALUE if buf is too small. */
+/* Writes the kernels of the plan in launch order, as "name<template
+ * arguments>" separated by ';' (the names a profiler shows, without namespace
+ * and parameter list) into buf (capacity len bytes, NUL-terminated).
+ * AC_ERR_INVALID_VALUE if buf is too small. These are the kernels of the form
+ * that column-major operands of any alignment can take (copies included), and
+ * of grouped and batched products the register-staged kernel; what a call on
+ * given operands launches is in adaptcore_call_info. */
 adaptcore_status adaptcore_plan_kernels(const adaptcore_plan_t* plan, char* buf, int64_t len);
+
+/* Fills *out with what one call of the plan on these operands launches. The
+ * operands' addresses and pitches (and, grouped and batched plans, the strides
+ * between their groups' matrices, 0 otherwise) decide whether a column-major
+ * operand is read in place, whether a grouped or batched product takes the
+ * direct-to-LDS tile, and which fallback serves misaligned rows. The operands
+ * are not read or checked. Works without a device. AC_ERR_INVALID_VALUE for a
+ * null plan or out; AC_ERR_UNSUPPORTED where the call would be refused for the
+ * operands' alignment. */
+adaptcore_status adaptcore_call_info(const adaptcore_plan_t* plan, const void* A, int64_t lda, int64_t stride_a,
+                                     const void* B, int64_t ldb, int64_t stride_b, adaptcore_call_desc_t* out);
 
 /* Lists the legal candidates of a shape with their model latencies, ordered
  * by the model's preference (best first). Returns the number of candidates

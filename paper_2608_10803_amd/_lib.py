@@ -64,6 +64,17 @@ class PlanDesc(ctypes.Structure):
         return d
 
 
+class CallDesc(ctypes.Structure):
+    _fields_ = [("variant_key", ctypes.c_uint64), ("in_place", ctypes.c_uint32), ("n_kernels", ctypes.c_int32),
+                ("workspace_bytes", ctypes.c_int64), ("predicted_s", ctypes.c_double),
+                ("kernels", ctypes.c_char * 256)]
+
+    def as_dict(self):
+        d = {f: getattr(self, f) for f, _ in self._fields_}
+        d["kernels"] = [k for k in self.kernels.decode().split(";") if k]
+        return d
+
+
 class Candidate(ctypes.Structure):
     _fields_ = [("variant_key", ctypes.c_uint64), ("cls", ctypes.c_int32), ("family", ctypes.c_int32),
                 ("tile_m", ctypes.c_int32), ("tile_n", ctypes.c_int32), ("tile_k", ctypes.c_int32),
@@ -171,6 +182,8 @@ def lib():
         L.adaptcore_plan_info.restype = i32
         L.adaptcore_plan_kernels.argtypes = [p, ctypes.c_char_p, i64]
         L.adaptcore_plan_kernels.restype = i32
+        L.adaptcore_call_info.argtypes = [p, p, i64, i64, p, i64, i64, ctypes.POINTER(CallDesc)]
+        L.adaptcore_call_info.restype = i32
         L.adaptcore_candidates.argtypes = [i64, i64, i64, i32, u32, ctypes.POINTER(Candidate), i64]
         L.adaptcore_candidates.restype = i64
         L.adaptcore_get_hw.argtypes = [ctypes.POINTER(Hw)]
@@ -337,10 +350,19 @@ def adaptcore_plan_info(plan):
 
 
 def adaptcore_plan_kernels(plan):
-    """Kernels one call of the plan launches, in launch order."""
+    """Kernels of the plan in launch order, in the form that operands of any
+    alignment can take (what a call launches: adaptcore_call_info)."""
     buf = ctypes.create_string_buffer(512)
     _check(lib().adaptcore_plan_kernels(plan, buf, len(buf)))
     return buf.value.decode().split(";")
+
+
+def adaptcore_call_info(plan, A, lda, B, ldb, stride_a=0, stride_b=0):
+    """What one call of the plan on these operands launches (dict: variant_key,
+    in_place, n_kernels, workspace_bytes, predicted_s, kernels)."""
+    d = CallDesc()
+    _check(lib().adaptcore_call_info(plan, A, lda, stride_a, B, ldb, stride_b, ctypes.byref(d)))
+    return d.as_dict()
 
 
 def adaptcore_candidates(M, N, K, dtype=AC_BF16_BF16OUT, layouts=AC_LAYOUT_ROW_ROW):

@@ -342,6 +342,111 @@ adaptcore_status adaptcore_reserve_workspace(void* stream, int64_t bytes) {
 
 namespace {
 
+// What one call of a plain plan runs on its operands.
+struct Route {
+  ac::Plan own;         // a fallback configuration
+  const ac::Plan* run;  // the configuration that runs: the plan's, or `own`
+  bool pads;            // operands reach the kernel as rows of whole 16-byte chunks
+  int lay;              // AC_LAYOUT_* bits of the column-major operands read in place
+  bool copy_a, copy_b;  // the copies made first (the tall-skinny kernel's B^T among them)
+  int launches;
+  Route() : run(nullptr), pads(false), lay(0), copy_a(false), copy_b(false), launches(0) {}
+  Route(const Route&) = delete;
+};
+
+// Column-major operand that the direct-to-LDS plan q reads in place (the
+// layout bit; 0: none): whole aligned 16-byte chunks in its rows as stored.
+// The tile of a column-major B is loaded as a row-major A's is, and the
+// reverse, so the result has the bits of the copied form without its prologue
+// (2048 x 14336 x 4096, B column-major: the copy took 44 of 285 us). B first:
+// one of the two at a time.
+int dl_in_place(const ac::Plan& q, const void* A, int64_t lda, const void* B, int64_t ldb) {
+  const int can = ac::kDlCfg[q.cfg].col;
+  if ((q.s.layouts & AC_LAYOUT_B_COL) && (can & 2) && ac::dl_a_aligned(B, ldb, q.s.K)) return AC_LAYOUT_B_COL;
+  if ((q.s.layouts & AC_LAYOUT_A_COL) && (can & 1) && ac::dl_b_aligned(A, lda, q.s.M)) return AC_LAYOUT_A_COL;
+  return 0;
+}
+
+adaptcore_status route_call(const ac::Plan& p, const void* A, int64_t lda, const void* B, int64_t ldb, Route* r) {
+  const int64_t N = p.s.N, K = p.s.K;
+  const bool a_col = (p.s.layouts & AC_LAYOUT_A_COL) != 0, b_col = (p.s.layouts & AC_LAYOUT_B_COL) != 0;
+  // Direct-to-LDS plans: operands the plan does not copy must have 16-byte
+  // aligned rows of whole chunks; otherwise the configuration's register-load
+  // form (if it has one, and K, N >= 8), else the register-staged sibling of
+  // the same tiling, runs on the operands as given (no padding copies).
+  // Off-chip accumulation plans load like the direct-to-LDS ones; with such
+  // operands the direct-to-LDS split-K plan of the same slices (same
+  // partials, same sum) runs instead, with its own fallbacks below.
+  r->run = &p;
+  bool dl = p.family == ac::FAM_DL || p.family == ac::FAM_DLSC;
+  if (dl && !p.unal) {  // (the register-load form takes any alignment)
+    const bool a_ok = a_col || p.ws_a_off >= 0 || ac::dl_a_aligned(A, lda, K);
+    const bool b_ok = b_col || p.ws_b_off >= 0 || ac::dl_b_aligned(B, ldb, N);
+    if (!(a_ok && b_ok)) {
+      if (p.family == ac::FAM_DLSC) {
+        adaptcore_hw_t hw;
+        {
+          std::lock_guard<std::mutex> lk(g_mu);
+          hw = g_hw;
+        }
+        const uint64_t key = ac::make_variant_key(ac::FAM_DL, p.cfg & 0xF, 0, p.pk, p.s.dtype, (int)p.s.layouts);
+        if (!ac::plan_for_key(p.s, hw, key, &r->own))
+          return fail(AC_ERR_UNSUPPORTED, "operands not aligned for this plan and no fallback applies");
+      } else {
+        r->own = p;
+      }
+      const ac::DlCfg& d = ac::kDlCfg[r->own.cfg];
+      // (column-major operands reach the kernel as aligned row-major copies)
+      if (d.unal && K >= 8 && N >= 8) {
+        r->own.unal = 1;
+      } else if (d.sibling >= 0) {
+        r->own.family = ac::FAM_TILE;
+        r->own.cfg = d.sibling;
+        dl = false;
+      } else {
+        return fail(AC_ERR_UNSUPPORTED, "operands not aligned for this configuration and no fallback applies");
+      }
+      r->run = &r->own;
+    }
+  }
+  // Tall-skinny plans of the direct-load form need A with 16-byte aligned
+  // rows; otherwise the configuration's register-load form runs if it has
+  // one, else the skinny-N kernel (any alignment) with the same split count
+  // if it has one, else unsplit.
+  if (p.family == ac::FAM_TALL && !p.unal && !ac::tall_a_aligned(A, lda, K)) {
+    if (ac::kTallCfg[p.cfg].unal) {
+      r->own = p;
+      r->own.unal = 1;
+    } else {
+      adaptcore_hw_t hw;
+      {
+        std::lock_guard<std::mutex> lk(g_mu);
+        hw = g_hw;
+      }
+      const int cfg = ac::kTallCfg[p.cfg].nt - 1;  // skinny-N configuration of the same column count
+      bool ok = false;
+      for (int pk : {p.pk, 1}) {
+        const uint64_t key = ac::make_variant_key(ac::FAM_SKINNY_N, cfg, 0, pk, p.s.dtype, (int)p.s.layouts);
+        if ((ok = ac::plan_for_key(p.s, hw, key, &r->own))) break;
+      }
+      if (!ok) return fail(AC_ERR_UNSUPPORTED, "A not aligned for this plan and no fallback applies");
+    }
+    r->run = &r->own;
+  }
+  const ac::Plan& q = *r->run;
+  if (q.family == ac::FAM_DL && !q.unal) r->lay = dl_in_place(q, A, lda, B, ldb);
+  // prologue: row-major copies of column-major operands, and zero-padded
+  // copies of unaligned row-major operands for the direct loads of a
+  // direct-to-LDS plan (rows of K and N rounded up to 8); the register-load
+  // form and the sibling read the row-major operands as given. A tall-skinny
+  // plan reads B's transposed copy (N x K8).
+  r->pads = dl && !q.unal;
+  r->copy_a = q.ws_a_off >= 0 && (a_col || r->pads) && !(r->lay & AC_LAYOUT_A_COL);
+  r->copy_b = q.ws_b_off >= 0 && (q.family == ac::FAM_TALL || b_col || r->pads) && !(r->lay & AC_LAYOUT_B_COL);
+  r->launches = q.n_launch - (q.ws_a_off >= 0) - (q.ws_b_off >= 0) + r->copy_a + r->copy_b;
+  return AC_OK;
+}
+
 // One call of a plain plan; epi != 0 selects the AddMM epilogue. With
 // `fixed` the workspace is the device scratch array of
 // adaptcore_matmul_noalloc (nothing is allocated).
@@ -391,90 +496,12 @@ adaptcore_status run_matmul(const adaptcore_plan_t* plan, const void* A, int64_t
   g.bias = bias;
   g.kB = K;
   g.nB = N;
-  // Direct-to-LDS plans: operands the plan does not copy must have 16-byte
-  // aligned rows of whole chunks; otherwise the configuration's register-load
-  // form (if it has one, and the operands are row-major with K, N >= 8), else
-  // the register-staged sibling of the same tiling, runs on the operands as
-  // given (no padding copies).
-  // Off-chip accumulation plans load like the direct-to-LDS ones; with such
-  // operands the direct-to-LDS split-K plan of the same slices (same
-  // partials, same sum) runs instead, with its own fallbacks below.
-  ac::Plan sib, dl_base;
-  const ac::Plan* src = &p;
-  if (p.family == ac::FAM_DLSC) {
-    const bool a_ok = a_col || p.ws_a_off >= 0 || ac::dl_a_aligned(A, lda, K);
-    const bool b_ok = b_col || p.ws_b_off >= 0 || ac::dl_b_aligned(B, ldb, N);
-    if (!(a_ok && b_ok)) {
-      adaptcore_hw_t hw;
-      {
-        std::lock_guard<std::mutex> lk(g_mu);
-        hw = g_hw;
-      }
-      const uint64_t key = ac::make_variant_key(ac::FAM_DL, p.cfg & 0xF, 0, p.pk, p.s.dtype, (int)p.s.layouts);
-      if (!ac::plan_for_key(p.s, hw, key, &dl_base))
-        return fail(AC_ERR_UNSUPPORTED, "operands not aligned for this plan and no fallback applies");
-      src = &dl_base;
-    }
-  }
-  const ac::Plan* run = src;
-  bool dl = src->family == ac::FAM_DL || src->family == ac::FAM_DLSC;
-  if (src->family == ac::FAM_DL && !src->unal) {  // (the register-load form takes any alignment)
-    const bool a_ok = a_col || src->ws_a_off >= 0 || ac::dl_a_aligned(A, lda, K);
-    const bool b_ok = b_col || src->ws_b_off >= 0 || ac::dl_b_aligned(B, ldb, N);
-    if (!(a_ok && b_ok)) {
-      sib = *src;
-      const ac::DlCfg& d = ac::kDlCfg[src->cfg];
-      // (column-major operands reach the kernel as aligned row-major copies)
-      if (d.unal && K >= 8 && N >= 8) {
-        sib.unal = 1;
-      } else if (d.sibling >= 0) {
-        sib.family = ac::FAM_TILE;
-        sib.cfg = d.sibling;
-        dl = false;
-      } else {
-        return fail(AC_ERR_UNSUPPORTED, "operands not aligned for this configuration and no fallback applies");
-      }
-      run = &sib;
-    }
-  }
-  // Tall-skinny plans of the direct-load form need A with 16-byte aligned
-  // rows; otherwise the configuration's register-load form runs if it has
-  // one, else the skinny-N kernel (any alignment) with the same split count
-  // if it has one, else unsplit.
-  if (p.family == ac::FAM_TALL && !p.unal && !ac::tall_a_aligned(A, lda, K) && ac::kTallCfg[p.cfg].unal) {
-    sib = p;
-    sib.unal = 1;
-    run = &sib;
-  } else if (p.family == ac::FAM_TALL && !p.unal && !ac::tall_a_aligned(A, lda, K)) {
-    adaptcore_hw_t hw;
-    {
-      std::lock_guard<std::mutex> lk(g_mu);
-      hw = g_hw;
-    }
-    const int cfg = ac::kTallCfg[p.cfg].nt - 1;  // skinny-N configuration of the same column count
-    bool ok = false;
-    for (int pk : {p.pk, 1}) {
-      const uint64_t key = ac::make_variant_key(ac::FAM_SKINNY_N, cfg, 0, pk, p.s.dtype, (int)p.s.layouts);
-      if ((ok = ac::plan_for_key(p.s, hw, key, &sib))) break;
-    }
-    if (!ok) return fail(AC_ERR_UNSUPPORTED, "A not aligned for this plan and no fallback applies");
-    run = &sib;
-  }
-  // the launch fields, workspace and prologue of the plan that runs
-  const ac::Plan& q = *run;
-  // A column-major operand whose rows (as stored) are whole aligned 16-byte
-  // chunks is read in place by the direct-to-LDS kernels that can: the tile of
-  // a column-major B is loaded as a row-major A's is, and the reverse, so the
-  // result has the bits of the copied form without its prologue (2048 x
-  // 14336 x 4096, B column-major: the copy took 44 of 285 us). B first: one of
-  // the two at a time.
-  if (q.family == ac::FAM_DL && !q.unal) {
-    const int can = ac::kDlCfg[q.cfg].col;
-    if (b_col && (can & 2) && ac::dl_a_aligned(B, ldb, K))
-      g.lay = 2;
-    else if (a_col && (can & 1) && ac::dl_b_aligned(A, lda, M))
-      g.lay = 1;
-  }
+  Route r;
+  st = route_call(p, A, lda, B, ldb, &r);
+  if (st != AC_OK) return st;
+  // the launch fields, workspace and prologue of the configuration that runs
+  const ac::Plan& q = *r.run;
+  g.lay = r.lay;
   g.pk = q.family == ac::FAM_STREAMK ? 1 : q.pk;
   g.kper = q.kper;
   g.tiles_m = q.pm;
@@ -503,15 +530,8 @@ adaptcore_status run_matmul(const adaptcore_plan_t* plan, const void* A, int64_t
     }
     g.ws = reinterpret_cast<float*>(w.ptr);
     char* base = static_cast<char*>(w.ptr);
-    // prologue: row-major copies of column-major operands, and zero-padded
-    // copies of unaligned row-major operands for the direct loads of a
-    // direct-to-LDS plan (rows of K and N rounded up to 8); the register-load
-    // form and the sibling read the row-major operands as given. A
-    // tall-skinny plan reads B's transposed copy (N x K8).
-    const bool pads = dl && !run->unal;
-    const bool tall = q.family == ac::FAM_TALL;
     const int64_t K8 = (K + 7) / 8 * 8, N8 = (N + 7) / 8 * 8;
-    if (tall && q.ws_b_off >= 0) {
+    if (r.copy_b && q.family == ac::FAM_TALL) {  // B^T: N x K8
       uint16_t* bt = reinterpret_cast<uint16_t*>(base + q.ws_b_off);
       const hipError_t e = b_col ? ac::launch_pad16(g.B, ldb, N, K, bt, K8, s)
                                  : ac::launch_transpose16(g.B, ldb, K, N, bt, K8, s);
@@ -519,7 +539,7 @@ adaptcore_status run_matmul(const adaptcore_plan_t* plan, const void* A, int64_t
       g.B = bt;
       g.ldb = K8;
     }
-    if (q.ws_a_off >= 0 && (a_col || pads) && !(g.lay & 1)) {
+    if (r.copy_a) {
       uint16_t* a2 = reinterpret_cast<uint16_t*>(base + q.ws_a_off);
       const hipError_t e = a_col ? ac::launch_transpose16(g.A, lda, K, M, a2, K8, s)
                                  : ac::launch_pad16(g.A, lda, M, K, a2, K8, s);
@@ -527,24 +547,24 @@ adaptcore_status run_matmul(const adaptcore_plan_t* plan, const void* A, int64_t
       g.A = a2;
       g.lda = K8;
     }
-    if (!tall && q.ws_b_off >= 0 && (b_col || pads) && !(g.lay & 2)) {
+    if (r.copy_b && q.family != ac::FAM_TALL) {
       uint16_t* b2 = reinterpret_cast<uint16_t*>(base + q.ws_b_off);
       const hipError_t e = b_col ? ac::launch_transpose16(g.B, ldb, N, K, b2, N8, s)
                                  : ac::launch_pad16(g.B, ldb, K, N, b2, N8, s);
       if (e != hipSuccess) return fail(AC_ERR_LAUNCH, std::string("kernel launch failed: ") + hipGetErrorString(e));
       g.B = b2;
       g.ldb = N8;
-      if (pads) g.nB = N8;
+      if (r.pads) g.nB = N8;
     }
     // the direct loads run over whole 8-element chunks of A's rows (zeros
     // past K in a copy); B's rows stay K. The register-load form reads the
     // operands as given and zero-fills past K itself.
-    if (pads) g.K = K8;
+    if (r.pads) g.K = K8;
   }
   const hipError_t e =
-      ac::dtype_f16_input(p.s.dtype) ? ac::f16::launch_plan(*run, g, s) : ac::launch_plan(*run, g, s);
+      ac::dtype_f16_input(p.s.dtype) ? ac::f16::launch_plan(q, g, s) : ac::launch_plan(q, g, s);
   if (e != hipSuccess) return fail(AC_ERR_LAUNCH, std::string("kernel launch failed: ") + hipGetErrorString(e));
-  st_launches.fetch_add((uint64_t)(q.n_launch - (g.lay != 0)), std::memory_order_relaxed);
+  st_launches.fetch_add((uint64_t)r.launches, std::memory_order_relaxed);
   return AC_OK;
 }
 
@@ -905,6 +925,48 @@ adaptcore_status adaptcore_plan_kernels(const adaptcore_plan_t* plan, char* buf,
   const std::string names = ac::kernel_names(plan->p);
   if (len < (int64_t)names.size() + 1) return fail(AC_ERR_INVALID_VALUE, "buffer too small");
   std::memcpy(buf, names.c_str(), names.size() + 1);
+  return AC_OK;
+}
+
+adaptcore_status adaptcore_call_info(const adaptcore_plan_t* plan, const void* A, int64_t lda, int64_t stride_a,
+                                     const void* B, int64_t ldb, int64_t stride_b, adaptcore_call_desc_t* out) {
+  if (!plan || !out) return fail(AC_ERR_INVALID_VALUE, "null argument");
+  const ac::Plan& p = plan->p;
+  std::memset(out, 0, sizeof *out);
+  out->variant_key = p.variant_key;
+  if (p.s.M == 0 || p.s.N == 0 || p.grid_x == 0) return AC_OK;
+  std::string names;
+  if (p.family == ac::FAM_GROUPED || p.family == ac::FAM_BATCHED) {
+    ac::GroupArgs a;
+    std::memset(&a, 0, sizeof a);
+    a.g.A = static_cast<const uint16_t*>(A);
+    a.g.B = static_cast<const uint16_t*>(B);
+    a.g.N = p.s.N;
+    a.g.K = p.s.K;
+    a.g.lda = lda;
+    a.g.ldb = ldb;
+    a.stride_a = p.family == ac::FAM_BATCHED ? stride_a : 0;
+    a.stride_b = stride_b;
+    a.groups = (int)p.groups;
+    names = ac::kernel_names(p, false, false, 0, ac::grouped_dl_runs(p, a));
+    out->n_kernels = p.n_launch;
+    out->predicted_s = p.predicted;
+  } else {
+    Route r;
+    const adaptcore_status st = route_call(p, A, lda, B, ldb, &r);
+    if (st != AC_OK) return st;
+    const ac::Plan& q = *r.run;
+    names = ac::kernel_names(q, r.copy_a, r.copy_b, r.lay, false);
+    out->variant_key = ac::make_variant_key(q.family, q.cfg, q.swizzle, q.pk, q.s.dtype, (int)q.s.layouts) |
+                       ((uint64_t)(q.unal & 1) << 13);
+    out->in_place = (uint32_t)r.lay;
+    if (q.family == ac::FAM_SKINNY_M) out->in_place |= q.s.layouts & AC_LAYOUT_B_COL;
+    out->n_kernels = r.launches;
+    out->workspace_bytes = q.ws_bytes;
+    out->predicted_s = q.predicted - (r.copy_a ? 0 : q.t_copy_a) - (r.copy_b ? 0 : q.t_copy_b);
+  }
+  if (names.size() >= sizeof out->kernels) return fail(AC_ERR_INTERNAL, "kernel names too long");
+  std::memcpy(out->kernels, names.c_str(), names.size() + 1);
   return AC_OK;
 }
 

@@ -2207,8 +2207,7 @@ hipError_t launch_grouped_plan(const Plan& p, const GroupArgs& a, hipStream_t st
   if ((p.family != FAM_GROUPED && p.family != FAM_BATCHED) || p.cfg < 0 || p.cfg >= N_TILE_CFG ||
       !kGroupedFns[p.cfg])
     return hipErrorInvalidValue;
-  const hipError_t e = (launch_grouped_dl_plan)(p, a, st);  // this format's (no argument-dependent lookup)
-  if (e != hipErrorNotSupported) return e;
+  if (ac::grouped_dl_runs(p, a)) return (launch_grouped_dl_plan)(p, a, st);  // this format's (no argument-dependent lookup)
   return kGroupedFns[p.cfg](p, a, st, dtype_out16(p.s.dtype));
 }
 

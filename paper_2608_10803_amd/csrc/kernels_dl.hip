@@ -1001,18 +1001,11 @@ hipError_t launch_dl_main(const Plan& p, const GemmArgs& g, hipStream_t st) {
   return kDlFns[p.cfg](p, g, st, dtype_out16(p.s.dtype));
 }
 
-// The grouped kernel of a tile configuration in its direct-to-LDS form;
-// hipErrorNotSupported where there is none or the operands are not aligned
-// (the caller then runs the register-staged one, which has the same bits).
-// Every group's operands must be aligned: the first one's, and the strides. A
-// single k-block leaves nothing to pipeline: 96 products of 200 x 200 x 64 run
-// in 6.5 us register-staged (128 x 64 tiles), 6.9 here at best.
+// The grouped kernel of a tile configuration in its direct-to-LDS form
+// (where grouped_dl_runs; the register-staged one has the same bits).
 hipError_t launch_grouped_dl_plan(const Plan& p, const GroupArgs& a, hipStream_t st) {
+  if (!ac::grouped_dl_runs(p, a)) return hipErrorInvalidValue;
   const GemmArgs& g = a.g;
-  const bool one = a.groups <= 1;
-  if (g.K < GROUPED_DL_MIN_K || !ac::dl_a_aligned(g.A, g.lda, g.K) || !ac::dl_b_aligned(g.B, g.ldb, g.N) ||
-      (!one && ((a.stride_a & 7) != 0 || (a.stride_b & 7) != 0)))
-    return hipErrorNotSupported;
   GroupArgs b = a;
   b.g.kB = g.K;
   b.g.nB = g.N;
@@ -1023,7 +1016,7 @@ hipError_t launch_grouped_dl_plan(const Plan& p, const GroupArgs& a, hipStream_t
   if (t.bm == 128 && t.bn == 128 && t.depth == 1) return launch_grouped_dl<128, 128, 64, 2>(p, b, st, obf);
   if (t.bm == 128 && t.bn == 128) return launch_grouped_dl<128, 128, 64, 3>(p, b, st, obf);
   if (t.bm == 64 && t.bn == 128) return launch_grouped_dl<64, 128, 64, 3>(p, b, st, obf);
-  return hipErrorNotSupported;
+  return hipErrorInvalidValue;
 }
 
 void query_occupancy_dl() {
@@ -1040,6 +1033,15 @@ bool dl_a_aligned(const void* A, int64_t lda, int64_t K) {
 }
 bool dl_b_aligned(const void* B, int64_t ldb, int64_t nB) {
   return (reinterpret_cast<uintptr_t>(B) & 15) == 0 && (ldb & 7) == 0 && (nB & 7) == 0 && ldb < DL_MAX_LD;
+}
+// Every group's operands must be aligned: the first one's, and the strides. A
+// single k-block leaves nothing to pipeline: 96 products of 200 x 200 x 64 run
+// in 6.5 us register-staged (128 x 64 tiles), 6.9 direct-to-LDS at best.
+bool grouped_dl_runs(const Plan& p, const GroupArgs& a) {
+  const GemmArgs& g = a.g;
+  return (p.family == FAM_GROUPED || p.family == FAM_BATCHED) && p.cfg >= 0 && p.cfg < N_TILE_CFG &&
+         kGroupedDlStages[p.cfg] > 0 && g.K >= GROUPED_DL_MIN_K && dl_a_aligned(g.A, g.lda, g.K) &&
+         dl_b_aligned(g.B, g.ldb, g.N) && (a.groups <= 1 || ((a.stride_a & 7) == 0 && (a.stride_b & 7) == 0));
 }
 // (an operand read in place column-major: rows of M, or of K)
 bool dl_operands_aligned(const GemmArgs& g) {

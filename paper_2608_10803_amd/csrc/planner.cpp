@@ -688,18 +688,18 @@ const int kSplits[] = {2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64, 80,
 // elements (16-byte aligned rows for the main kernels).
 void add_prologue(const Shape& s, const adaptcore_hw_t& hw, Plan* p) {
   p->ws_a_off = p->ws_b_off = -1;
-  p->t_pro = 0;
+  p->t_copy_a = p->t_copy_b = 0;
   p->rank = p->predicted;
   if (s.M == 0 || s.N == 0 || s.K == 0) return;
   double in_place = 0;
   // `direct`: the main kernel reads this operand without the copy when its
   // rows are aligned (the copy's workspace stays part of the plan: the
   // operands of a call decide)
-  auto copy = [&](int64_t rows, int64_t cols, int64_t* off, bool direct = false) {
+  auto copy = [&](int64_t rows, int64_t cols, int64_t* off, double* tc, bool direct = false) {
     *off = (p->ws_bytes + 255) / 256 * 256;
     p->ws_bytes = *off + rows * ldw8(cols) * 2;
     const double t = hw.t_launch + 4.0 * (double)rows * (double)cols / (hw.hbm_bw * hw.hbm_eta);
-    p->t_pro += t;
+    *tc = t;
     if (direct) in_place += t;
     p->n_launch += 1;
   };
@@ -713,18 +713,19 @@ void add_prologue(const Shape& s, const adaptcore_hw_t& hw, Plan* p) {
   // direct-to-LDS, 12.3 small-M at M = 4); beyond, the measured order decides
   // (4 x 4096 x 14336: 24.5 against 29.4 us, 16 x 14336 x 4096: 26.2, 31.3).
   const bool b_rank = b_in && (s.M > 64 || s.K * s.N > (int64_t)4096 * 4096);
-  if (s.layouts & AC_LAYOUT_A_COL) copy(s.M, s.K, &p->ws_a_off, a_in);
+  if (s.layouts & AC_LAYOUT_A_COL) copy(s.M, s.K, &p->ws_a_off, &p->t_copy_a, a_in);
   // the padding prologue of the direct-to-LDS kernels: a row-major operand
   // whose rows are not whole 16-byte chunks is copied zero-padded
-  else if ((p->family == FAM_DL || p->family == FAM_DLSC) && !p->unal && (s.K % 8) != 0) copy(s.M, s.K, &p->ws_a_off);
+  else if ((p->family == FAM_DL || p->family == FAM_DLSC) && !p->unal && (s.K % 8) != 0)
+    copy(s.M, s.K, &p->ws_a_off, &p->t_copy_a);
   // the small-M kernel reads a column-major B in place (its MFMA fragments
   // are runs of k), so only the other families copy B; the tall-skinny
   // kernel reads B's transposed copy (N x K, rows padded to 8) in any case
-  if (p->family == FAM_TALL) copy(s.N, s.K, &p->ws_b_off);
-  else if ((s.layouts & AC_LAYOUT_B_COL) && p->family != FAM_SKINNY_M) copy(s.K, s.N, &p->ws_b_off, b_rank);
+  if (p->family == FAM_TALL) copy(s.N, s.K, &p->ws_b_off, &p->t_copy_b);
+  else if ((s.layouts & AC_LAYOUT_B_COL) && p->family != FAM_SKINNY_M) copy(s.K, s.N, &p->ws_b_off, &p->t_copy_b, b_rank);
   else if (!(s.layouts & AC_LAYOUT_B_COL) && (p->family == FAM_DL || p->family == FAM_DLSC) && !p->unal && (s.N % 8) != 0)
-    copy(s.K, s.N, &p->ws_b_off);
-  p->predicted += p->t_pro;
+    copy(s.K, s.N, &p->ws_b_off, &p->t_copy_b);
+  p->predicted += p->t_copy_a + p->t_copy_b;
   p->rank = p->predicted - in_place;
 }
 
@@ -1299,11 +1300,13 @@ bool batched_for_key(const Shape& s, int64_t batch, const adaptcore_hw_t& hw, ui
   return true;
 }
 
-static std::string kernel_names_fmt(const Plan& p);
+static std::string kernel_names_fmt(const Plan& p, int lay, bool grouped_dl);
 
-std::string kernel_names(const Plan& p) {
+std::string kernel_names(const Plan& p) { return kernel_names(p, p.ws_a_off >= 0, p.ws_b_off >= 0, 0, false); }
+
+std::string kernel_names(const Plan& p, bool copy_a, bool copy_b, int lay, bool grouped_dl) {
   // the fp16-input kernels live in the nested namespace f16
-  std::string r = kernel_names_fmt(p);
+  std::string r = kernel_names_fmt(p, lay, grouped_dl);
   if (dtype_f16_input(p.s.dtype) && !r.empty()) {
     std::string out = "f16::";
     for (char ch : r) {
@@ -1316,12 +1319,12 @@ std::string kernel_names(const Plan& p) {
   // column-major operand, the padding copy otherwise) runs first
   // (the tall-skinny kernel's copy of B is B^T: a transpose of a row-major B)
   const bool b_tr = ((p.s.layouts & AC_LAYOUT_B_COL) != 0) != (p.family == FAM_TALL);
-  if (p.ws_b_off >= 0) r = std::string(b_tr ? "k_transpose16;" : "k_pad16;") + r;
-  if (p.ws_a_off >= 0) r = std::string((p.s.layouts & AC_LAYOUT_A_COL) ? "k_transpose16;" : "k_pad16;") + r;
+  if (copy_b) r = std::string(b_tr ? "k_transpose16;" : "k_pad16;") + r;
+  if (copy_a) r = std::string((p.s.layouts & AC_LAYOUT_A_COL) ? "k_transpose16;" : "k_pad16;") + r;
   return r;
 }
 
-static std::string kernel_names_fmt(const Plan& p) {
+static std::string kernel_names_fmt(const Plan& p, int lay, bool grouped_dl) {
   const int obf = dtype_out16(p.s.dtype);
   const char* b = obf ? "true" : "false";
   char buf[160];
@@ -1367,6 +1370,11 @@ static std::string kernel_names_fmt(const Plan& p) {
     case FAM_GROUPED:
     case FAM_BATCHED: {
       const TileCfg& t = kTileCfg[p.cfg];
+      if (grouped_dl) {
+        std::snprintf(buf, sizeof buf, "k_grouped_dl<%d, %d, %d, %d, %d>", t.bm, t.bn, TILE_BK, kGroupedDlStages[p.cfg],
+                      obf);
+        return buf;
+      }
       std::snprintf(buf, sizeof buf, "k_grouped<%d, %d, %d, %d, %d>", t.bm, t.bn, t.ms, obf, t.depth);
       return buf;
     }
@@ -1378,9 +1386,11 @@ static std::string kernel_names_fmt(const Plan& p) {
     }
     case FAM_DL: {
       const DlCfg& d = kDlCfg[p.cfg];
-      std::snprintf(buf, sizeof buf, "%s<%d, %d, %d, %d, %d>", p.unal ? "k_dlu" : "k_dl", d.bm, d.bn, d.bk, d.stages,
-                    p.pk > 1 ? 2 : obf);
+      std::snprintf(buf, sizeof buf, "%s<%d, %d, %d, %d, %d", p.unal ? "k_dlu" : lay ? "k_dlc" : "k_dl", d.bm, d.bn,
+                    d.bk, d.stages, p.pk > 1 ? 2 : obf);
       std::string r(buf);
+      if (!p.unal && lay) r += ", " + std::to_string(lay);
+      r += ">";
       if (p.pk > 1) r += std::string(";k_reduce<") + b + ">";
       return r;
     }

@@ -38,7 +38,7 @@ struct Plan {
   // Prologue (Eq. 7's T_pro): byte offsets in the workspace of the row-major
   // copies of a column-major A (M x ld8(K)) and B (K x ld8(N)); -1: none.
   int64_t ws_a_off = -1, ws_b_off = -1;
-  double t_pro = 0;      // its model time, included in `predicted`
+  double t_copy_a = 0, t_copy_b = 0;  // its copies' model times, included in `predicted`
   int n_candidates = 0;
   double predicted = 0;
   // the search's order: `predicted`, less the copy of a column-major operand
@@ -87,9 +87,12 @@ bool batched_for_key(const Shape& s, int64_t batch, const adaptcore_hw_t& hw, ui
 // dimensions below 2^17; larger shapes set bit 63 and hash all fields.
 uint64_t shape_key(const Shape& s, bool* exact);
 
-// Kernels one call of the plan launches, ';'-separated (template arguments
-// as a profiler prints them).
+// Kernels a call of the plan launches, ';'-separated (template arguments as a
+// profiler prints them): with every copy the plan provides for, or with the
+// copies given and, direct-to-LDS plans, the operands read in place in `lay`
+// (layout bits), grouped and batched ones the direct-to-LDS form (grouped_dl).
 std::string kernel_names(const Plan& p);
+std::string kernel_names(const Plan& p, bool copy_a, bool copy_b, int lay, bool grouped_dl);
 
 // Index of a configuration in the calibrated cost tables of the profile.
 int config_index(int family, int cfg);

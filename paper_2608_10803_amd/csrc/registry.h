@@ -26,7 +26,9 @@ hipError_t launch_pad16(const uint16_t* src, int64_t ld_src, int64_t rows, int64
 hipError_t launch_dl_main(const Plan& p, const GemmArgs& g, hipStream_t st);
 hipError_t launch_dl_sc_main(const Plan& p, const GemmArgs& g, hipStream_t st);
 // A grouped or batched plan's product on the direct-to-LDS tile of the same
-// tiling; hipErrorNotSupported (nothing launched) if it cannot run there.
+// tiling: whether these operands run there (configuration, K and alignment),
+// and the launch if they do.
+bool grouped_dl_runs(const Plan& p, const GroupArgs& a);
 hipError_t launch_grouped_dl_plan(const Plan& p, const GroupArgs& a, hipStream_t st);
 void query_occupancy_dl();
 // Tall-skinny streaming kernel (kernels_tall.hip): A's alignment (16-byte
@@ -55,9 +57,6 @@ namespace f16 {
 hipError_t launch_plan(const Plan& p, const GemmArgs& g, hipStream_t st);
 hipError_t launch_dl_main(const Plan& p, const GemmArgs& g, hipStream_t st);
 hipError_t launch_dl_sc_main(const Plan& p, const GemmArgs& g, hipStream_t st);
-// A grouped or batched plan's product on the direct-to-LDS tile of the same
-// tiling; hipErrorNotSupported (nothing launched) if it cannot run there.
-hipError_t launch_grouped_dl_plan(const Plan& p, const GroupArgs& a, hipStream_t st);
 hipError_t launch_grouped_dl_plan(const Plan& p, const GroupArgs& a, hipStream_t st);
 void query_occupancy_dl();
 hipError_t launch_tall_main(const Plan& p, const GemmArgs& g, hipStream_t st);

@@ -34,6 +34,10 @@ static_assert(sizeof(kGroupedCfg) / sizeof(kGroupedCfg[0]) == N_TILE_CFG, "group
 // Grouped and batched products of at least this K (two k-blocks) run on the
 // direct-to-LDS tile where their operands are aligned.
 constexpr int64_t GROUPED_DL_MIN_K = TILE_BK + 1;
+// LDS stages of a tile configuration's grouped direct-to-LDS kernel, which has
+// its tile and 64-deep k-blocks (0: it has none).
+constexpr int kGroupedDlStages[] = {0, 3, 3, 2, 0, 3, 0, 0, 3, 0, 0};
+static_assert(sizeof(kGroupedDlStages) / sizeof(kGroupedDlStages[0]) == N_TILE_CFG, "grouped direct-to-LDS kernels");
 
 // Tile configurations that also have a persistent kernel (one k-block of
 // global loads ahead, carried across tiles): the depth-1 configurations.

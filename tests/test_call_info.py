@@ -1,0 +1,113 @@
+"""What a call launches on given operands (adaptcore_call_info), on the CPU:
+column-major operands read in place or copied, the fallbacks of misaligned
+rows, and the two forms of the grouped kernel."""
+import random
+
+import pytest
+
+import paper_2608_10803_amd as ac
+
+F32, BF16, F16 = ac.AC_BF16_F32OUT, ac.AC_BF16_BF16OUT, ac.AC_F16_F16OUT
+A0, B0 = 0x10000, 0x20000  # aligned addresses; never read
+
+
+def info(plan, M, N, K, layouts=0, a_off=0, b_off=0, a_pad=0, b_pad=0):
+    """Operands `off` elements past an aligned address, their stored rows `pad`
+    elements longer than the matrix."""
+    lda, ldb = (M if layouts & 1 else K) + a_pad, (K if layouts & 2 else N) + b_pad
+    return ac.adaptcore_call_info(plan, A0 + 2 * a_off, lda, B0 + 2 * b_off, ldb)
+
+
+def candidates(M, N, K, dtype, layouts, family):
+    for c in ac.adaptcore_candidates(M, N, K, dtype, layouts):
+        if c["family"] == family:
+            yield ac.adaptcore_plan_variant(M, N, K, dtype, layouts, c["variant_key"]), c
+
+
+@pytest.mark.parametrize("layouts,bad", [(1, {"a_off": 1}), (1, {"a_pad": 3}), (2, {"b_off": 1}), (2, {"b_pad": 4})])
+def test_in_place_or_copied(layouts, bad):
+    seen = 0
+    for M, N, K in [(136, 520, 264), (2048, 14336, 4096), (16, 14336, 4096)]:
+        for plan, c in candidates(M, N, K, BF16, layouts, ac.AC_FAMILY_DL):
+            whole, d = ac.adaptcore_plan_kernels(plan), ac.adaptcore_plan_info(plan)
+            got = info(plan, M, N, K, layouts, **bad)
+            assert got["kernels"] == whole and got["in_place"] == 0 and got["n_kernels"] == len(whole), (c, got)
+            assert got["predicted_s"] == d["predicted_s"] and got["variant_key"] == c["variant_key"]
+            got = info(plan, M, N, K, layouts)
+            assert got["n_kernels"] == len(got["kernels"]) and got["variant_key"] == c["variant_key"]
+            if got["in_place"]:
+                seen += 1
+                name = whole[1].replace("k_dl<", "k_dlc<").replace(">", ", %d>" % layouts)
+                assert got["in_place"] == layouts and got["kernels"] == [name] + whole[2:], (got, whole)
+                assert got["predicted_s"] < d["predicted_s"]
+            else:  # the 64 x 512 tile, and tiles of fewer than 128 rows for A
+                assert got["kernels"] == whole and (c["tile_m"] < 128 if layouts == 1 else c["tile_n"] == 512), (c, got)
+    assert seen >= 20
+
+
+def test_one_operand_of_two_in_place():
+    for plan, c in candidates(264, 520, 328, BF16, 3, ac.AC_FAMILY_DL):
+        both = info(plan, 264, 520, 328, 3)
+        only_a = info(plan, 264, 520, 328, 3, b_off=1)
+        copied = info(plan, 264, 520, 328, 3, a_off=1, b_off=1)
+        assert both["in_place"] == (0 if c["tile_n"] == 512 else 2)
+        assert only_a["in_place"] == (1 if c["tile_m"] >= 128 else 0)
+        assert copied["in_place"] == 0 and copied["kernels"].count("k_transpose16") == 2
+        assert both["kernels"].count("k_transpose16") == 2 - (both["in_place"] != 0)
+
+
+def test_row_major_plans_and_fallbacks():
+    rng = random.Random(7)
+    shapes = [tuple(int(2 ** rng.uniform(0, 12)) for _ in range(3)) for _ in range(40)] + [(520, 333, 265)]
+    for M, N, K in shapes:
+        for dtype in (BF16, F32, F16):
+            plan = ac.adaptcore_plan(M, N, K, dtype)
+            got = info(plan, M, N, K)
+            assert got["kernels"] == ac.adaptcore_plan_kernels(plan) and got["n_kernels"] == len(got["kernels"])
+            assert got["variant_key"] == ac.adaptcore_plan_info(plan)["variant_key"] and got["in_place"] == 0
+    # misaligned rows of operands that are not copied: the register-load form, or the tile kernel
+    for plan, c in candidates(512, 512, 512, BF16, 0, ac.AC_FAMILY_DL):
+        got = info(plan, 512, 512, 512, a_off=1)
+        assert got["kernels"][0].startswith(("k_dlu<", "k_tile<")), got
+        assert got["variant_key"] != c["variant_key"] and got["n_kernels"] == len(got["kernels"])
+    # a misaligned B beside an A that the plan would pad: no copy at all
+    for plan, c in candidates(512, 512, 515, BF16, 0, ac.AC_FAMILY_DL):
+        if (c["variant_key"] >> 13) & 1:
+            continue
+        assert info(plan, 512, 512, 515)["kernels"][0] == "k_pad16"
+        got = info(plan, 512, 512, 515, b_off=1)
+        assert "k_pad16" not in got["kernels"] and got["n_kernels"] == len(got["kernels"]), got
+    # nothing to launch
+    got = info(ac.adaptcore_plan(0, 8, 8, BF16), 0, 8, 8)
+    assert got["kernels"] == [] and got["n_kernels"] == 0
+    with pytest.raises(ac.AdaptCoreError) as e:
+        ac.adaptcore_call_info(None, A0, 8, B0, 8)
+    assert e.value.status == ac.AC_ERR_INVALID_VALUE
+
+
+@pytest.mark.parametrize("dtype", [BF16, F32, F16])
+def test_grouped_forms(dtype):
+    dl = (1, 2, 3, 5, 8)  # tile configurations with a direct-to-LDS kernel
+    ns = "f16::" if dtype == F16 else ""
+    seen = set()
+    for make, fam, args in [
+            (lambda k, K, N: ac.adaptcore_grouped_plan_variant(500, 7, N, K, dtype, 0, k), ac.AC_FAMILY_GROUPED, (0,)),
+            (lambda k, K, N: ac.adaptcore_batched_plan_variant(6, 130, N, K, dtype, 0, k), ac.AC_FAMILY_BATCHED, (1,))]:
+        for cfg in range(11):
+            for N, K in [(264, 200), (264, 64), (260, 200), (264, 196)]:
+                key = fam | (cfg << 4) | (1 << 12) | (1 << 16) | (dtype << 48)
+                try:
+                    plan = make(key, K, N)
+                except ac.AdaptCoreError:
+                    continue
+                sa = 130 * K if args[0] else 0
+                for off, lda, ldb, stride, ok in [(0, K, N, K * N, True), (1, K, N, K * N, False),
+                                                  (0, K + 4, N, K * N, False), (0, K, N + 8, K * (N + 8), True),
+                                                  (0, K, N, K * N + 4, False)]:
+                    got = ac.adaptcore_call_info(plan, A0 + 2 * off, lda, B0, ldb, stride_a=sa, stride_b=stride)
+                    direct = ok and cfg in dl and N % 8 == 0 and K % 8 == 0 and K > 64
+                    assert got["kernels"][0].startswith(ns + ("k_grouped_dl<" if direct else "k_grouped<")), (cfg, got)
+                    assert got["n_kernels"] == 1 and got["workspace_bytes"] == 0
+                    if direct:
+                        seen.add(cfg)
+    assert seen == set(dl)
