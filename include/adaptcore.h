@@ -71,7 +71,8 @@ enum { AC_FP16_F32OUT = AC_F16_F32OUT, AC_FP16_FP16OUT = AC_F16_F16OUT };
  * Eq. 7), except a column-major B under the small-M kernel, which reads it
  * in place, and one column-major operand (B if both are) under the
  * direct-to-LDS tiles where its stored rows are whole aligned 16-byte chunks:
- * the plan keeps the copy and its workspace, the operands of a call decide.
+ * the operands of a call decide, and a call takes workspace for the copies it
+ * makes.
  * Grouped and batched products take row-major operands only. */
 enum { AC_LAYOUT_ROW_ROW = 0, AC_LAYOUT_A_COL = 1, AC_LAYOUT_B_COL = 2, AC_LAYOUT_COL_COL = 3 };
 /* The same bits named per operand (A_ROWMAJOR | B_COLMAJOR, ...). */
@@ -314,8 +315,8 @@ adaptcore_status adaptcore_matmul(const adaptcore_plan_t* plan, const void* A, i
  * (64 MiB) on every GPU the library runs on, held until the process ends.
  * No call of this entry point allocates or frees device memory. The
  * caller still passes A, B and C; arguments and checks are those of
- * adaptcore_matmul, and a plan whose workspace_bytes exceed the array gives
- * AC_ERR_UNSUPPORTED (nothing launched). Every call on one GPU shares that
+ * adaptcore_matmul, and a call whose workspace (adaptcore_call_info) exceeds
+ * the array gives AC_ERR_UNSUPPORTED (nothing launched). Every call on one GPU shares that
  * GPU's array, and the array keeps the last call's contents: no part of it
  * needs clearing (every byte a call reads was written earlier in the same
  * call), but calls that overlap in time on one GPU (different streams, or

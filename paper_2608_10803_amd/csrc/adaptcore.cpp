@@ -349,8 +349,10 @@ struct Route {
   bool pads;            // operands reach the kernel as rows of whole 16-byte chunks
   int lay;              // AC_LAYOUT_* bits of the column-major operands read in place
   bool copy_a, copy_b;  // the copies made first (the tall-skinny kernel's B^T among them)
+  int64_t off_a, off_b;  // where they go in the workspace, after the partials
+  int64_t ws_bytes;      // workspace of this call
   int launches;
-  Route() : run(nullptr), pads(false), lay(0), copy_a(false), copy_b(false), launches(0) {}
+  Route() : run(nullptr), pads(false), lay(0), copy_a(false), copy_b(false), off_a(0), off_b(0), ws_bytes(0), launches(0) {}
   Route(const Route&) = delete;
 };
 
@@ -443,6 +445,13 @@ adaptcore_status route_call(const ac::Plan& p, const void* A, int64_t lda, const
   r->pads = dl && !q.unal;
   r->copy_a = q.ws_a_off >= 0 && (a_col || r->pads) && !(r->lay & AC_LAYOUT_A_COL);
   r->copy_b = q.ws_b_off >= 0 && (q.family == ac::FAM_TALL || b_col || r->pads) && !(r->lay & AC_LAYOUT_B_COL);
+  // the plan's workspace without the copies this call does not make: 117 MB
+  // of transposed weights for a 4 x 4096 x 14336 call that reads them in place
+  const int64_t end_a = q.ws_b_off >= 0 ? q.ws_b_off : q.ws_bytes;
+  const int64_t partials = q.ws_a_off >= 0 ? q.ws_a_off : end_a;
+  r->off_a = partials;
+  r->off_b = r->off_a + (r->copy_a ? end_a - q.ws_a_off : 0);
+  r->ws_bytes = r->off_b + (r->copy_b ? q.ws_bytes - q.ws_b_off : 0);
   r->launches = q.n_launch - (q.ws_a_off >= 0) - (q.ws_b_off >= 0) + r->copy_a + r->copy_b;
   return AC_OK;
 }
@@ -511,11 +520,11 @@ adaptcore_status run_matmul(const adaptcore_plan_t* plan, const void* A, int64_t
   g.sk_tiles = q.sk_tiles;
   g.ws_pk = q.ws_pk;
   g.grid = q.grid_x;
-  if (q.ws_bytes > 0) {
+  if (r.ws_bytes > 0) {
     Workspace w;
     if (fixed) {
-      if (q.ws_bytes > ac::NOALLOC_SCRATCH_BYTES)
-        return fail(AC_ERR_UNSUPPORTED, "the plan's workspace (" + std::to_string(q.ws_bytes) +
+      if (r.ws_bytes > ac::NOALLOC_SCRATCH_BYTES)
+        return fail(AC_ERR_UNSUPPORTED, "the call's workspace (" + std::to_string(r.ws_bytes) +
                                             " bytes) exceeds the no-allocation scratch of " +
                                             std::to_string(ac::NOALLOC_SCRATCH_BYTES) + " bytes");
       int dev = 0;
@@ -525,14 +534,14 @@ adaptcore_status run_matmul(const adaptcore_plan_t* plan, const void* A, int64_t
       w.ptr = static_cast<char*>(ptr);
       w.bytes = ac::NOALLOC_SCRATCH_BYTES;
     } else {
-      st = get_workspace(s, q.ws_bytes, &w);
+      st = get_workspace(s, r.ws_bytes, &w);
       if (st != AC_OK) return st;
     }
     g.ws = reinterpret_cast<float*>(w.ptr);
     char* base = static_cast<char*>(w.ptr);
     const int64_t K8 = (K + 7) / 8 * 8, N8 = (N + 7) / 8 * 8;
     if (r.copy_b && q.family == ac::FAM_TALL) {  // B^T: N x K8
-      uint16_t* bt = reinterpret_cast<uint16_t*>(base + q.ws_b_off);
+      uint16_t* bt = reinterpret_cast<uint16_t*>(base + r.off_b);
       const hipError_t e = b_col ? ac::launch_pad16(g.B, ldb, N, K, bt, K8, s)
                                  : ac::launch_transpose16(g.B, ldb, K, N, bt, K8, s);
       if (e != hipSuccess) return fail(AC_ERR_LAUNCH, std::string("kernel launch failed: ") + hipGetErrorString(e));
@@ -540,7 +549,7 @@ adaptcore_status run_matmul(const adaptcore_plan_t* plan, const void* A, int64_t
       g.ldb = K8;
     }
     if (r.copy_a) {
-      uint16_t* a2 = reinterpret_cast<uint16_t*>(base + q.ws_a_off);
+      uint16_t* a2 = reinterpret_cast<uint16_t*>(base + r.off_a);
       const hipError_t e = a_col ? ac::launch_transpose16(g.A, lda, K, M, a2, K8, s)
                                  : ac::launch_pad16(g.A, lda, M, K, a2, K8, s);
       if (e != hipSuccess) return fail(AC_ERR_LAUNCH, std::string("kernel launch failed: ") + hipGetErrorString(e));
@@ -548,7 +557,7 @@ adaptcore_status run_matmul(const adaptcore_plan_t* plan, const void* A, int64_t
       g.lda = K8;
     }
     if (r.copy_b && q.family != ac::FAM_TALL) {
-      uint16_t* b2 = reinterpret_cast<uint16_t*>(base + q.ws_b_off);
+      uint16_t* b2 = reinterpret_cast<uint16_t*>(base + r.off_b);
       const hipError_t e = b_col ? ac::launch_transpose16(g.B, ldb, N, K, b2, N8, s)
                                  : ac::launch_pad16(g.B, ldb, K, N, b2, N8, s);
       if (e != hipSuccess) return fail(AC_ERR_LAUNCH, std::string("kernel launch failed: ") + hipGetErrorString(e));
@@ -556,11 +565,11 @@ adaptcore_status run_matmul(const adaptcore_plan_t* plan, const void* A, int64_t
       g.ldb = N8;
       if (r.pads) g.nB = N8;
     }
-    // the direct loads run over whole 8-element chunks of A's rows (zeros
-    // past K in a copy); B's rows stay K. The register-load form reads the
-    // operands as given and zero-fills past K itself.
-    if (r.pads) g.K = K8;
   }
+  // the direct loads run over whole 8-element chunks of A's rows (zeros past K
+  // in a copy); B's rows stay K. The register-load form reads the operands as
+  // given and zero-fills past K itself.
+  if (r.pads) g.K = (K + 7) / 8 * 8;
   const hipError_t e =
       ac::dtype_f16_input(p.s.dtype) ? ac::f16::launch_plan(q, g, s) : ac::launch_plan(q, g, s);
   if (e != hipSuccess) return fail(AC_ERR_LAUNCH, std::string("kernel launch failed: ") + hipGetErrorString(e));
@@ -962,7 +971,7 @@ adaptcore_status adaptcore_call_info(const adaptcore_plan_t* plan, const void* A
     out->in_place = (uint32_t)r.lay;
     if (q.family == ac::FAM_SKINNY_M) out->in_place |= q.s.layouts & AC_LAYOUT_B_COL;
     out->n_kernels = r.launches;
-    out->workspace_bytes = q.ws_bytes;
+    out->workspace_bytes = r.ws_bytes;
     out->predicted_s = q.predicted - (r.copy_a ? 0 : q.t_copy_a) - (r.copy_b ? 0 : q.t_copy_b);
   }
   if (names.size() >= sizeof out->kernels) return fail(AC_ERR_INTERNAL, "kernel names too long");

@@ -45,6 +45,21 @@ def test_in_place_or_copied(layouts, bad):
     assert seen >= 20
 
 
+def test_workspace_is_that_of_the_copies_made():
+    up = lambda n: -(-n // 256) * 256
+    for M, N, K in [(4, 4096, 14336), (136, 520, 264)]:
+        for layouts in (1, 2, 3):
+            for plan, c in candidates(M, N, K, F32, layouts, ac.AC_FAMILY_DL):
+                part = up(c["pk"] * M * -(-N // 8) * 8 * 4) if c["pk"] > 1 else 0
+                size_a, size_b = up(2 * M * K) if layouts & 1 else 0, 2 * K * -(-N // 8) * 8 if layouts & 2 else 0
+                got = info(plan, M, N, K, layouts)
+                want = part + (size_a if not got["in_place"] & 1 else 0) + (size_b if not got["in_place"] & 2 else 0)
+                assert up(got["workspace_bytes"]) == up(want), (c, got, want)
+                copied = info(plan, M, N, K, layouts, a_off=1, b_off=1)
+                if copied["variant_key"] == c["variant_key"]:  # (a misaligned row-major operand takes another form)
+                    assert copied["workspace_bytes"] == ac.adaptcore_plan_info(plan)["workspace_bytes"]
+
+
 def test_one_operand_of_two_in_place():
     for plan, c in candidates(264, 520, 328, BF16, 3, ac.AC_FAMILY_DL):
         both = info(plan, 264, 520, 328, 3)

@@ -3,8 +3,9 @@ device scratch as workspace, checked through the C ABI against
 adaptcore_matmul (same plan, same kernels: equal bit for bit) and against
 the oracle, on two calls in a row, the second with a smaller input; a
 split-K plan, a column-major operand (prologue copy in the scratch), a plan
-without workspace, and a plan whose workspace exceeds the scratch (refused,
-nothing written)."""
+without workspace, decode products whose column-major weights (read in place)
+are larger than the scratch, and a plan whose workspace exceeds the scratch
+(refused, nothing written)."""
 import numpy as np
 import pytest
 
@@ -91,6 +92,53 @@ def test_noalloc_default_plans_and_column_major():
         v1, v2 = _vals(C1, F32), _vals(C2, F32)
         assert np.array_equal(v1.view(np.uint64), v2.view(np.uint64)), (M, N, K, lay)
         assert gemm_ref.err_metric(v1, R, D) <= tol(F32), (M, N, K, lay)
+
+
+def _decode_weights(M, N, K, b_off):
+    """A, B stored N x K `b_off` elements past an aligned address, and the
+    product and its absolute-value product in 64 bits on the device."""
+    t = torch()
+    g = t.Generator(device="cuda").manual_seed(M + N + K)
+    A = t.empty(M, K, dtype=t.float32, device="cuda").uniform_(-1, 1, generator=g).bfloat16()
+    B = t.empty(N * K + b_off, dtype=t.float32, device="cuda").uniform_(-1, 1, generator=g).bfloat16()[b_off:]
+    Ad, Bd = A.double(), B.view(N, K).double().t().contiguous()
+    return A, B, (Ad @ Bd, Ad.abs() @ Bd.abs())
+
+
+def _close(C, ref):
+    R, D = (x.cpu().numpy() for x in ref)
+    assert gemm_ref.err_metric(_vals(C, F32), R, D) <= tol(F32)
+
+
+# weights of 117 MB: read in place
+@pytest.mark.parametrize("shape", [(4, 4096, 14336), (16, 14336, 4096), (64, 8192, 8192)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_noalloc_decode_weights_larger_than_the_scratch(shape):
+    M, N, K = shape
+    A, B, ref = _decode_weights(M, N, K, 0)
+    plan = ac.adaptcore_plan(M, N, K, F32, ac.AC_LAYOUT_B_COL)
+    C1, C2 = _both(plan, A, K, B, K, M, N, F32, 0)
+    assert bool((C1 == C2).all())
+    _close(C1, ref)
+
+
+def test_capture_of_decode_weights_needs_the_partials_only():
+    t = torch()
+    M, N, K = 4, 4096, 14336
+    A, B, ref = _decode_weights(M, N, K, 0)
+    plan = ac.adaptcore_plan(M, N, K, F32, ac.AC_LAYOUT_B_COL)
+    s = t.cuda.Stream()
+    ac.adaptcore_reserve_workspace(s.cuda_stream, 4 << 20)
+    C = t.empty(M, N, dtype=t.float32, device="cuda")
+    g = t.cuda.CUDAGraph()
+    with t.cuda.graph(g, stream=s):
+        ac.adaptcore_matmul(plan, A.data_ptr(), K, B.data_ptr(), K, C.data_ptr(), N, s.cuda_stream)
+    for _ in range(3):
+        C.fill_(float("nan"))
+        t.cuda.synchronize()
+        g.replay()
+        t.cuda.synchronize()
+        _close(C, ref)
 
 
 def test_noalloc_refuses_a_workspace_beyond_the_scratch():
