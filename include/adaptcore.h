@@ -129,7 +129,8 @@ typedef struct {
   int32_t dtype;
   uint32_t layouts;
   uint64_t shape_key;   /* 64-bit key of the shape (cache index) */
-  uint64_t variant_key; /* 64-bit key of the selected configuration */
+  uint64_t variant_key; /* 64-bit key of the selected configuration (a call whose column-major
+                           operand cannot be read in place may run another: adaptcore_call_info) */
   int32_t cls;          /* adaptcore_class of the taxonomy for this shape */
   int32_t family;       /* adaptcore_family of the selected kernel */
   int32_t tile_m, tile_n, tile_k; /* m1, n1, k1 (workgroup output tile, k granule) */

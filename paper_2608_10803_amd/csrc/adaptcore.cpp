@@ -8,6 +8,7 @@
 #include <chrono>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <tuple>
@@ -20,6 +21,10 @@
 
 struct adaptcore_plan_s {
   ac::Plan p;
+  // Where the search counted on an operand read in place (p.in_place) and
+  // another configuration is the best one with every column-major operand
+  // copied: that one, for the calls whose operand cannot be read in place.
+  std::unique_ptr<ac::Plan> alt;
 };
 
 namespace {
@@ -156,6 +161,12 @@ adaptcore_plan_s* plan_miss(const ac::Shape& s) {
   auto* p = new adaptcore_plan_s{c.front()};
   bool exact;
   p->p.shape_key = ac::shape_key(s, &exact);
+  if (p->p.in_place) {
+    const ac::Plan& copied = *std::min_element(c.begin(), c.end(), [](const ac::Plan& a, const ac::Plan& b) {
+      return a.predicted != b.predicted ? a.predicted < b.predicted : a.variant_key < b.variant_key;
+    });
+    if (copied.variant_key != p->p.variant_key) p->alt.reset(new ac::Plan(copied));
+  }
   g_owned.push_back(p);
   st_miss_seconds += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   st_misses.fetch_add(1, std::memory_order_relaxed);
@@ -369,7 +380,22 @@ int dl_in_place(const ac::Plan& q, const void* A, int64_t lda, const void* B, in
   return 0;
 }
 
-adaptcore_status route_call(const ac::Plan& p, const void* A, int64_t lda, const void* B, int64_t ldb, Route* r) {
+// Whether operands meet a direct-to-LDS plan's direct loads: those it does not
+// copy have 16-byte aligned rows of whole chunks.
+bool dl_loads(const ac::Plan& p, const void* A, int64_t lda, const void* B, int64_t ldb) {
+  return ((p.s.layouts & AC_LAYOUT_A_COL) || p.ws_a_off >= 0 || ac::dl_a_aligned(A, lda, p.s.K)) &&
+         ((p.s.layouts & AC_LAYOUT_B_COL) || p.ws_b_off >= 0 || ac::dl_b_aligned(B, ldb, p.s.N));
+}
+
+adaptcore_status route_call(const adaptcore_plan_s& plan, const void* A, int64_t lda, const void* B, int64_t ldb,
+                            Route* r) {
+  // A search that counted on reading an operand in place (in_place) took a
+  // configuration which, with that operand copied, may be far from the best:
+  // 4 x 4096 x 14336 with B one element past an aligned address runs in
+  // 58 us on the small-M kernel, which reads such a B, and in 77 us copied.
+  const bool in_place = !plan.alt || (dl_loads(plan.p, A, lda, B, ldb) &&
+                                      (dl_in_place(plan.p, A, lda, B, ldb) & plan.p.in_place) != 0);
+  const ac::Plan& p = in_place ? plan.p : *plan.alt;
   const int64_t N = p.s.N, K = p.s.K;
   const bool a_col = (p.s.layouts & AC_LAYOUT_A_COL) != 0, b_col = (p.s.layouts & AC_LAYOUT_B_COL) != 0;
   // Direct-to-LDS plans: operands the plan does not copy must have 16-byte
@@ -382,9 +408,7 @@ adaptcore_status route_call(const ac::Plan& p, const void* A, int64_t lda, const
   r->run = &p;
   bool dl = p.family == ac::FAM_DL || p.family == ac::FAM_DLSC;
   if (dl && !p.unal) {  // (the register-load form takes any alignment)
-    const bool a_ok = a_col || p.ws_a_off >= 0 || ac::dl_a_aligned(A, lda, K);
-    const bool b_ok = b_col || p.ws_b_off >= 0 || ac::dl_b_aligned(B, ldb, N);
-    if (!(a_ok && b_ok)) {
+    if (!dl_loads(p, A, lda, B, ldb)) {
       if (p.family == ac::FAM_DLSC) {
         adaptcore_hw_t hw;
         {
@@ -506,7 +530,7 @@ adaptcore_status run_matmul(const adaptcore_plan_t* plan, const void* A, int64_t
   g.kB = K;
   g.nB = N;
   Route r;
-  st = route_call(p, A, lda, B, ldb, &r);
+  st = route_call(*plan, A, lda, B, ldb, &r);
   if (st != AC_OK) return st;
   // the launch fields, workspace and prologue of the configuration that runs
   const ac::Plan& q = *r.run;
@@ -924,7 +948,7 @@ adaptcore_status adaptcore_plan_info(const adaptcore_plan_t* plan, adaptcore_pla
   out->swizzle = p.swizzle;
   out->n_candidates = p.n_candidates;
   out->predicted_s = p.predicted;
-  out->workspace_bytes = p.ws_bytes;
+  out->workspace_bytes = std::max(p.ws_bytes, plan->alt ? plan->alt->ws_bytes : 0);
   out->groups = p.groups;
   return AC_OK;
 }
@@ -962,7 +986,7 @@ adaptcore_status adaptcore_call_info(const adaptcore_plan_t* plan, const void* A
     out->predicted_s = p.predicted;
   } else {
     Route r;
-    const adaptcore_status st = route_call(p, A, lda, B, ldb, &r);
+    const adaptcore_status st = route_call(*plan, A, lda, B, ldb, &r);
     if (st != AC_OK) return st;
     const ac::Plan& q = *r.run;
     names = ac::kernel_names(q, r.copy_a, r.copy_b, r.lay, false);

@@ -727,6 +727,7 @@ void add_prologue(const Shape& s, const adaptcore_hw_t& hw, Plan* p) {
     copy(s.K, s.N, &p->ws_b_off, &p->t_copy_b);
   p->predicted += p->t_copy_a + p->t_copy_b;
   p->rank = p->predicted - in_place;
+  p->in_place = b_rank ? AC_LAYOUT_B_COL : a_in ? AC_LAYOUT_A_COL : 0;
 }
 
 // Direct-to-LDS configuration whose costs price a grouped tile configuration

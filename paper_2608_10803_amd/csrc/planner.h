@@ -44,6 +44,7 @@ struct Plan {
   // the search's order: `predicted`, less the copy of a column-major operand
   // that the direct-to-LDS kernel reads in place where its rows are aligned
   double rank = 0;
+  int in_place = 0;      // layout bit of that operand (0: none)
   int64_t groups = 0;    // grouped product: groups (s.M is then the row capacity);
                          // strided batch: batch count (s is every batch's shape)
 };

@@ -71,6 +71,41 @@ def test_one_operand_of_two_in_place():
         assert both["kernels"].count("k_transpose16") == 2 - (both["in_place"] != 0)
 
 
+# (the last two: A misaligned, which takes the register-load form and would copy B)
+@pytest.mark.parametrize("bad", [{"b_off": 1}, {"b_pad": 4}, {"a_off": 1}, {"a_pad": 3}])
+def test_decode_weights_that_cannot_be_read_in_place(bad):
+    """The planned configuration reads aligned weights in place; other operands
+    take the best configuration of the search with every copy counted, which
+    for large weights is the small-M kernel (any alignment, no copy)."""
+    rng = random.Random(3)
+    shapes = [(4, 4096, 14336), (16, 14336, 4096), (32, 8192, 8192), (1, 14336, 4096)]
+    while len(shapes) < 60:
+        M, N, K = rng.choice([1, 2, 5, 16, 33, 64]), int(2 ** rng.uniform(10, 14)), int(2 ** rng.uniform(10, 14)) // 8 * 8
+        shapes.append((M, N, K))
+    small_m = 0
+    for M, N, K in shapes:
+        plan = ac.adaptcore_plan(M, N, K, BF16, 2)
+        cands = ac.adaptcore_candidates(M, N, K, BF16, 2)
+        best = min(cands, key=lambda c: (c["predicted_s"], c["variant_key"]))
+        got = info(plan, M, N, K, 2, **bad)
+        d = ac.adaptcore_plan_info(plan)
+        assert got["workspace_bytes"] <= d["workspace_bytes"]
+        if d["family"] != ac.AC_FAMILY_DL or not info(plan, M, N, K, 2)["in_place"]:
+            assert got["variant_key"] == d["variant_key"]
+        elif best["family"] == ac.AC_FAMILY_SKINNY_M:
+            small_m += 1
+            assert got["variant_key"] == best["variant_key"] and got["predicted_s"] == best["predicted_s"]
+            assert "k_transpose16" not in got["kernels"], (M, N, K, got)
+            assert got["workspace_bytes"] <= 16 << 20  # partials
+        elif "b_off" in bad or "b_pad" in bad:
+            assert got["variant_key"] == best["variant_key"], (M, N, K, got, best)
+    assert small_m >= 10
+    # a forced configuration runs whatever the alignment
+    for plan, c in candidates(4, 4096, 14336, BF16, 2, ac.AC_FAMILY_DL):
+        got = info(plan, 4, 4096, 14336, 2, b_off=1)
+        assert got["kernels"][0] == "k_transpose16" and got["variant_key"] == c["variant_key"]
+
+
 def test_row_major_plans_and_fallbacks():
     rng = random.Random(7)
     shapes = [tuple(int(2 ** rng.uniform(0, 12)) for _ in range(3)) for _ in range(40)] + [(520, 333, 265)]

@@ -122,6 +122,22 @@ def test_noalloc_decode_weights_larger_than_the_scratch(shape):
     _close(C1, ref)
 
 
+# weights that cannot be read in place, one element past an aligned address or
+# of an odd pitch: the small-M kernel, no copy of them
+@pytest.mark.parametrize("shape,b_off", [((4, 4096, 14336), 1), ((16, 14336, 4096), 1), ((4, 4096, 14331), 0)],
+                         ids=["4x4096x14336+1", "16x14336x4096+1", "4x4096x14331"])
+def test_noalloc_misaligned_decode_weights(shape, b_off):
+    M, N, K = shape
+    A, B, ref = _decode_weights(M, N, K, b_off)
+    plan = ac.adaptcore_plan(M, N, K, F32, ac.AC_LAYOUT_B_COL)
+    call = ac.adaptcore_call_info(plan, A.data_ptr(), K, B.data_ptr(), K)
+    n0 = ac.adaptcore_stats()["launches"]
+    C1, C2 = _both(plan, A, K, B, K, M, N, F32, 0)
+    assert call["n_kernels"] <= 2 and ac.adaptcore_stats()["launches"] - n0 == 2 * call["n_kernels"], call
+    assert bool((C1 == C2).all())
+    _close(C1, ref)
+
+
 def test_capture_of_decode_weights_needs_the_partials_only():
     t = torch()
     M, N, K = 4, 4096, 14336
