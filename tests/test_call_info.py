@@ -71,6 +71,23 @@ def test_one_operand_of_two_in_place():
         assert both["kernels"].count("k_transpose16") == 2 - (both["in_place"] != 0)
 
 
+def test_in_place_weights_at_every_size():
+    """No size of B at which a plan goes back to a kernel priced higher: the pick
+    has the lowest prediction among the configurations, each with the copies
+    that a call on aligned operands makes."""
+    rng = random.Random(5)
+    shapes = [(M, 4096, K) for M in (1, 4, 16, 64) for K in (1024, 4088, 4096, 4104)]
+    while len(shapes) < 60:
+        shapes.append((int(2 ** rng.uniform(0, 8)), int(2 ** rng.uniform(4, 13)), int(2 ** rng.uniform(4, 13)) // 8 * 8))
+    for M, N, K in shapes:
+        t = {}
+        for c in ac.adaptcore_candidates(M, N, K, BF16, 2):
+            plan = ac.adaptcore_plan_variant(M, N, K, BF16, 2, c["variant_key"])
+            t[c["variant_key"]] = info(plan, M, N, K, 2)["predicted_s"]
+        got = info(ac.adaptcore_plan(M, N, K, BF16, 2), M, N, K, 2)
+        assert got["predicted_s"] == pytest.approx(min(t.values()), rel=1e-12), (M, N, K, got)
+
+
 # (the last two: A misaligned, which takes the register-load form and would copy B)
 @pytest.mark.parametrize("bad", [{"b_off": 1}, {"b_pad": 4}, {"a_off": 1}, {"a_pad": 3}])
 def test_decode_weights_that_cannot_be_read_in_place(bad):

@@ -236,9 +236,13 @@ def test_layout_plans():
                 if layouts & 2 and skinny:
                     rest = [n.replace("k_skinny_m<", "k_skinny_m_bt<") for n in rest]
                 assert names[len(copies):] == rest, (names, rest)
-        # the decode shape with B column-major picks the in-place small-M kernel
+        # the decode shape with B column-major picks a kernel that reads it in place; misaligned rows take
+        # the small-M kernel, which reads any
         if (M, N, K) == (4, 4096, 4096):
-            names = ac.adaptcore_plan_kernels(ac.adaptcore_plan(M, N, K, ac.AC_BF16_BF16OUT, 2))
+            h = ac.adaptcore_plan(M, N, K, ac.AC_BF16_BF16OUT, 2)
+            got = ac.adaptcore_call_info(h, 0x1000, K, 0x2000, K)
+            assert got["in_place"] == 2 and "k_transpose16" not in got["kernels"], got
+            names = ac.adaptcore_call_info(h, 0x1000, K, 0x2002, K)["kernels"]
             assert names[0].startswith("k_skinny_m_bt<"), names
     # K == 0: nothing to copy
     d = ac.adaptcore_plan_info(ac.adaptcore_plan(30, 40, 0, ac.AC_BF16_F32OUT, 3))
