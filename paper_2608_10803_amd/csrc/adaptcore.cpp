@@ -24,6 +24,8 @@ struct adaptcore_plan_s {
   // Where the search counted on an operand read in place (p.in_place) and
   // another configuration is the best one with every column-major operand
   // copied: that one, for the calls whose operand cannot be read in place.
+  // Grouped and batched plans: the configuration for operands that the
+  // direct-to-LDS kernels do not take, where it is another one.
   std::unique_ptr<ac::Plan> alt;
 };
 
@@ -653,13 +655,14 @@ const adaptcore_plan_t* adaptcore_grouped_plan(int64_t rows, int64_t groups, int
   const auto t0 = std::chrono::steady_clock::now();
   ac::Plan p;
   const ac::Shape s{rows, N, K, dtype, layouts};
-  if (!ac::plan_grouped(s, groups, g_hw, &p)) {
+  if (!ac::plan_grouped(s, groups, g_hw, true, &p)) {
     fail(AC_ERR_UNSUPPORTED, "no grouped configuration fits (launch grid too large)");
     return nullptr;
   }
   bool exact;
   p.shape_key = ac::shape_key(s, &exact);
   auto* pp = new adaptcore_plan_s{p};
+  if (ac::plan_grouped(s, groups, g_hw, false, &p) && p.variant_key != pp->p.variant_key) pp->alt.reset(new ac::Plan(p));
   g_owned.push_back(pp);
   g_grouped[k] = pp;
   st_miss_seconds += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -700,6 +703,20 @@ const adaptcore_plan_t* adaptcore_grouped_plan_variant(int64_t rows, int64_t gro
 
 namespace {
 
+// The configuration that runs on a grouped or batched call's operands, and its
+// launch fields. A tiling picked at the direct-to-LDS costs would be a poor
+// one for the register-staged kernel that misaligned operands take.
+const ac::Plan& route_group(const adaptcore_plan_s& plan, ac::GroupArgs* a) {
+  const ac::Plan& q = plan.alt && !ac::grouped_dl_aligned(*a) ? *plan.alt : plan.p;
+  a->g.kper = q.kper;
+  a->g.tiles_m = q.pm;
+  a->g.tiles_n = q.pn;
+  a->g.swizzle = q.swizzle;
+  a->slots = q.pm;
+  if (q.family == ac::FAM_BATCHED) a->tiles_per_group = (int)((q.s.M + q.tile_m - 1) / q.tile_m);
+  return q;
+}
+
 // One call of a grouped plan; epi != 0 selects the AddMM epilogue (bias rows
 // stride_bias apart, one per group).
 adaptcore_status run_grouped(const adaptcore_plan_t* plan, const int32_t* counts, const void* A, int64_t lda,
@@ -735,10 +752,6 @@ adaptcore_status run_grouped(const adaptcore_plan_t* plan, const int32_t* counts
   a.g.ldb = ldb;
   a.g.ldc = ldc;
   a.g.pk = 1;
-  a.g.kper = p.kper;
-  a.g.tiles_m = p.pm;
-  a.g.tiles_n = p.pn;
-  a.g.swizzle = p.swizzle;
   a.g.epi = epi;
   a.g.alpha = alpha;
   a.g.beta = beta;
@@ -748,9 +761,9 @@ adaptcore_status run_grouped(const adaptcore_plan_t* plan, const int32_t* counts
   a.stride_b = stride_b;
   a.stride_bias = stride_bias;
   a.groups = (int)p.groups;
-  a.slots = p.pm;
-  const hipError_t e = ac::dtype_f16_input(p.s.dtype) ? ac::f16::launch_grouped_plan(p, a, static_cast<hipStream_t>(stream))
-                                                       : ac::launch_grouped_plan(p, a, static_cast<hipStream_t>(stream));
+  const ac::Plan& q = route_group(*plan, &a);
+  const hipError_t e = ac::dtype_f16_input(p.s.dtype) ? ac::f16::launch_grouped_plan(q, a, static_cast<hipStream_t>(stream))
+                                                       : ac::launch_grouped_plan(q, a, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(AC_ERR_LAUNCH, std::string("kernel launch failed: ") + hipGetErrorString(e));
   st_launches.fetch_add(1, std::memory_order_relaxed);
   return AC_OK;
@@ -798,13 +811,14 @@ const adaptcore_plan_t* adaptcore_batched_plan(int64_t batch, int64_t M, int64_t
   const auto t0 = std::chrono::steady_clock::now();
   ac::Plan p;
   const ac::Shape s{M, N, K, dtype, layouts};
-  if (!ac::plan_batched(s, batch, g_hw, &p)) {
+  if (!ac::plan_batched(s, batch, g_hw, true, &p)) {
     fail(AC_ERR_UNSUPPORTED, "no batched configuration fits (launch grid too large)");
     return nullptr;
   }
   bool exact;
   p.shape_key = ac::shape_key(s, &exact);
   auto* pp = new adaptcore_plan_s{p};
+  if (ac::plan_batched(s, batch, g_hw, false, &p) && p.variant_key != pp->p.variant_key) pp->alt.reset(new ac::Plan(p));
   g_owned.push_back(pp);
   g_batched[k] = pp;
   st_miss_seconds += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -883,10 +897,6 @@ adaptcore_status run_batched(const adaptcore_plan_t* plan, const void* A, int64_
   a.g.ldb = ldb;
   a.g.ldc = ldc;
   a.g.pk = 1;
-  a.g.kper = p.kper;
-  a.g.tiles_m = p.pm;
-  a.g.tiles_n = p.pn;
-  a.g.swizzle = p.swizzle;
   a.g.epi = epi;
   a.g.alpha = alpha;
   a.g.beta = beta;
@@ -897,10 +907,9 @@ adaptcore_status run_batched(const adaptcore_plan_t* plan, const void* A, int64_
   a.stride_b = stride_b;
   a.stride_c = stride_c;
   a.groups = (int)batch;
-  a.slots = p.pm;
-  a.tiles_per_group = (int)((M + p.tile_m - 1) / p.tile_m);
-  const hipError_t e = ac::dtype_f16_input(p.s.dtype) ? ac::f16::launch_grouped_plan(p, a, static_cast<hipStream_t>(stream))
-                                                       : ac::launch_grouped_plan(p, a, static_cast<hipStream_t>(stream));
+  const ac::Plan& q = route_group(*plan, &a);
+  const hipError_t e = ac::dtype_f16_input(p.s.dtype) ? ac::f16::launch_grouped_plan(q, a, static_cast<hipStream_t>(stream))
+                                                       : ac::launch_grouped_plan(q, a, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(AC_ERR_LAUNCH, std::string("kernel launch failed: ") + hipGetErrorString(e));
   st_launches.fetch_add(1, std::memory_order_relaxed);
   return AC_OK;
@@ -981,9 +990,11 @@ adaptcore_status adaptcore_call_info(const adaptcore_plan_t* plan, const void* A
     a.stride_a = p.family == ac::FAM_BATCHED ? stride_a : 0;
     a.stride_b = stride_b;
     a.groups = (int)p.groups;
-    names = ac::kernel_names(p, false, false, 0, ac::grouped_dl_runs(p, a));
-    out->n_kernels = p.n_launch;
-    out->predicted_s = p.predicted;
+    const ac::Plan& q = route_group(*plan, &a);
+    names = ac::kernel_names(q, false, false, 0, ac::grouped_dl_runs(q, a));
+    out->variant_key = q.variant_key;
+    out->n_kernels = q.n_launch;
+    out->predicted_s = q.predicted;
   } else {
     Route r;
     const adaptcore_status st = route_call(*plan, A, lda, B, ldb, &r);

@@ -1037,11 +1037,14 @@ bool dl_b_aligned(const void* B, int64_t ldb, int64_t nB) {
 // Every group's operands must be aligned: the first one's, and the strides. A
 // single k-block leaves nothing to pipeline: 96 products of 200 x 200 x 64 run
 // in 6.5 us register-staged (128 x 64 tiles), 6.9 direct-to-LDS at best.
-bool grouped_dl_runs(const Plan& p, const GroupArgs& a) {
+bool grouped_dl_aligned(const GroupArgs& a) {
   const GemmArgs& g = a.g;
+  return g.K >= GROUPED_DL_MIN_K && dl_a_aligned(g.A, g.lda, g.K) && dl_b_aligned(g.B, g.ldb, g.N) &&
+         (a.groups <= 1 || ((a.stride_a & 7) == 0 && (a.stride_b & 7) == 0));
+}
+bool grouped_dl_runs(const Plan& p, const GroupArgs& a) {
   return (p.family == FAM_GROUPED || p.family == FAM_BATCHED) && p.cfg >= 0 && p.cfg < N_TILE_CFG &&
-         kGroupedDlStages[p.cfg] > 0 && g.K >= GROUPED_DL_MIN_K && dl_a_aligned(g.A, g.lda, g.K) &&
-         dl_b_aligned(g.B, g.ldb, g.N) && (a.groups <= 1 || ((a.stride_a & 7) == 0 && (a.stride_b & 7) == 0));
+         kGroupedDlStages[p.cfg] > 0 && grouped_dl_aligned(a);
 }
 // (an operand read in place column-major: rows of M, or of K)
 bool dl_operands_aligned(const GemmArgs& g) {

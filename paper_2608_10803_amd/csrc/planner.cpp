@@ -746,12 +746,12 @@ bool finish(const Ctx& c, Plan* p, const Work& w) {
 }
 
 // Work of one group's product on the grouped kernels. With K and N multiples
-// of 8 the direct-to-LDS kernel of the same tiling runs where there is one
-// (aligned operands), so its costs apply.
-bool group_work(const Ctx& c, int cfg, int swizzle, Plan* one, Work* w) {
+// of 8 and aligned operands (`direct`) the direct-to-LDS kernel of the same
+// tiling runs where there is one, so its costs apply.
+bool group_work(const Ctx& c, int cfg, int swizzle, bool direct, Plan* one, Work* w) {
   if (!build_tile(c, cfg, 1, swizzle, one, w)) return false;
   const int d = kGroupedDl[cfg];
-  if (d < 0 || c.s.K < GROUPED_DL_MIN_K || c.s.K % 8 != 0 || c.s.N % 8 != 0) return true;
+  if (!direct || d < 0 || c.s.K < GROUPED_DL_MIN_K || c.s.K % 8 != 0 || c.s.N % 8 != 0) return true;
   const DlCfg& t = kDlCfg[d];
   w->idx = IDX_DL + d;
   w->occ = occupancy(FAM_DL, d);
@@ -766,7 +766,8 @@ bool group_work(const Ctx& c, int cfg, int swizzle, Plan* one, Work* w) {
 // tile -- times the column tiles. Model: the counts are on the device, so
 // the plan assumes the balanced split (ne groups of rows / ne rows) and
 // prices it as ne independent products of that shape sharing the GPU.
-bool build_grouped(const Shape& s, int64_t groups, const adaptcore_hw_t& hw, int cfg, int swizzle, Plan* p) {
+bool build_grouped(const Shape& s, int64_t groups, const adaptcore_hw_t& hw, int cfg, int swizzle, bool direct,
+                   Plan* p) {
   if (cfg < 0 || cfg >= N_TILE_CFG || !kGroupedCfg[cfg]) return false;
   const TileCfg& t = kTileCfg[cfg];
   if (tile_lds_bytes(t) > hw.lds_bytes) return false;
@@ -802,7 +803,7 @@ bool build_grouped(const Shape& s, int64_t groups, const adaptcore_hw_t& hw, int
   const Ctx c{sg, hw, compulsory, out_bytes(s.dtype), unaligned};
   Plan one;
   Work w;
-  if (!group_work(c, cfg, swizzle, &one, &w)) return false;
+  if (!group_work(c, cfg, swizzle, direct, &one, &w)) return false;
   w.units *= ne;
   w.total_read *= (double)ne;
   w.total_write *= (double)ne;
@@ -1193,7 +1194,8 @@ bool plan_for_key(const Shape& s, const adaptcore_hw_t& hw, uint64_t key, Plan* 
 // The grouped kernel over a strided batch: every group has the shape s, so
 // the grid is exact (batch x row tiles x column tiles) and the model prices
 // `batch` independent products of shape s sharing the GPU.
-bool build_batched(const Shape& s, int64_t batch, const adaptcore_hw_t& hw, int cfg, int swizzle, Plan* p) {
+bool build_batched(const Shape& s, int64_t batch, const adaptcore_hw_t& hw, int cfg, int swizzle, bool direct,
+                   Plan* p) {
   if (cfg < 0 || cfg >= N_TILE_CFG || !kGroupedCfg[cfg]) return false;
   const TileCfg& t = kTileCfg[cfg];
   if (tile_lds_bytes(t) > hw.lds_bytes) return false;
@@ -1227,7 +1229,7 @@ bool build_batched(const Shape& s, int64_t batch, const adaptcore_hw_t& hw, int 
   const Ctx c{s, hw, compulsory, out_bytes(s.dtype), unaligned};
   Plan one;
   Work w;
-  if (!group_work(c, cfg, swizzle, &one, &w)) return false;
+  if (!group_work(c, cfg, swizzle, direct, &one, &w)) return false;
   w.units *= batch;
   w.total_read *= (double)batch;
   w.total_write *= (double)batch;
@@ -1235,12 +1237,12 @@ bool build_batched(const Shape& s, int64_t batch, const adaptcore_hw_t& hw, int 
   return true;
 }
 
-bool plan_grouped(const Shape& s, int64_t groups, const adaptcore_hw_t& hw, Plan* out) {
+bool plan_grouped(const Shape& s, int64_t groups, const adaptcore_hw_t& hw, bool direct, Plan* out) {
   bool found = false;
   int n = 0;
   for (int cfg = 0; cfg < N_TILE_CFG; ++cfg) {
     Plan p;
-    if (!build_grouped(s, groups, hw, cfg, 1, &p)) continue;
+    if (!build_grouped(s, groups, hw, cfg, 1, direct, &p)) continue;
     ++n;
     if (!found || p.predicted < out->predicted) {
       *out = p;
@@ -1260,7 +1262,7 @@ bool grouped_for_key(const Shape& s, int64_t groups, const adaptcore_hw_t& hw, u
       vk_layouts(key) != (int)s.layouts)
     return false;
   Plan p;
-  if (!build_grouped(s, groups, hw, vk_cfg(key), vk_swizzle(key), &p) || p.variant_key != key) return false;
+  if (!build_grouped(s, groups, hw, vk_cfg(key), vk_swizzle(key), true, &p) || p.variant_key != key) return false;
   int base = 0;
   p.n_candidates = 1;
   p.cls = classify_shape(s, hw, &base);
@@ -1268,12 +1270,12 @@ bool grouped_for_key(const Shape& s, int64_t groups, const adaptcore_hw_t& hw, u
   return true;
 }
 
-bool plan_batched(const Shape& s, int64_t batch, const adaptcore_hw_t& hw, Plan* out) {
+bool plan_batched(const Shape& s, int64_t batch, const adaptcore_hw_t& hw, bool direct, Plan* out) {
   bool found = false;
   int n = 0;
   for (int cfg = 0; cfg < N_TILE_CFG; ++cfg) {
     Plan p;
-    if (!build_batched(s, batch, hw, cfg, 1, &p)) continue;
+    if (!build_batched(s, batch, hw, cfg, 1, direct, &p)) continue;
     ++n;
     if (!found || p.predicted < out->predicted) {
       *out = p;
@@ -1293,7 +1295,7 @@ bool batched_for_key(const Shape& s, int64_t batch, const adaptcore_hw_t& hw, ui
       vk_layouts(key) != (int)s.layouts)
     return false;
   Plan p;
-  if (!build_batched(s, batch, hw, vk_cfg(key), vk_swizzle(key), &p) || p.variant_key != key) return false;
+  if (!build_batched(s, batch, hw, vk_cfg(key), vk_swizzle(key), true, &p) || p.variant_key != key) return false;
   int base = 0;
   p.n_candidates = 1;
   p.cls = classify_shape(s, hw, &base);

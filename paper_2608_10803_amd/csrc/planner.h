@@ -76,12 +76,14 @@ bool plan_for_key(const Shape& s, const adaptcore_hw_t& hw, uint64_t key, Plan* 
 
 // Grouped product of `groups` groups over a row capacity of s.M rows: the
 // model's choice among the grouped tile configurations (plan_grouped), or
-// one configuration forced by its key (grouped_for_key).
-bool plan_grouped(const Shape& s, int64_t groups, const adaptcore_hw_t& hw, Plan* out);
+// one configuration forced by its key (grouped_for_key). `direct`: for
+// operands that the direct-to-LDS kernels take (grouped_dl_aligned), else for
+// the register-staged ones.
+bool plan_grouped(const Shape& s, int64_t groups, const adaptcore_hw_t& hw, bool direct, Plan* out);
 bool grouped_for_key(const Shape& s, int64_t groups, const adaptcore_hw_t& hw, uint64_t key, Plan* out);
 
 // Strided batch of `batch` products of shape s on the grouped kernel.
-bool plan_batched(const Shape& s, int64_t batch, const adaptcore_hw_t& hw, Plan* out);
+bool plan_batched(const Shape& s, int64_t batch, const adaptcore_hw_t& hw, bool direct, Plan* out);
 bool batched_for_key(const Shape& s, int64_t batch, const adaptcore_hw_t& hw, uint64_t key, Plan* out);
 
 // 64-bit shape key: M | N << 17 | K << 34 | dtype << 51 | layouts << 55, for

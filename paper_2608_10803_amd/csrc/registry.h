@@ -26,8 +26,9 @@ hipError_t launch_pad16(const uint16_t* src, int64_t ld_src, int64_t rows, int64
 hipError_t launch_dl_main(const Plan& p, const GemmArgs& g, hipStream_t st);
 hipError_t launch_dl_sc_main(const Plan& p, const GemmArgs& g, hipStream_t st);
 // A grouped or batched plan's product on the direct-to-LDS tile of the same
-// tiling: whether these operands run there (configuration, K and alignment),
-// and the launch if they do.
+// tiling: whether these operands can run there (K and every group's
+// alignment) and this configuration does, and the launch if it does.
+bool grouped_dl_aligned(const GroupArgs& a);
 bool grouped_dl_runs(const Plan& p, const GroupArgs& a);
 hipError_t launch_grouped_dl_plan(const Plan& p, const GroupArgs& a, hipStream_t st);
 void query_occupancy_dl();

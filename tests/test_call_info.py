@@ -178,3 +178,30 @@ def test_grouped_forms(dtype):
                     if direct:
                         seen.add(cfg)
     assert seen == set(dl)
+
+
+# (kind, groups, rows, N, K): tile configuration for aligned and for misaligned operands, with the planner's
+# table of workgroups per CU
+GROUP_PICKS = [("g", 64, 8192, 1536, 4096, 2, 3), ("g", 6, 1744, 440, 1344, 5, 6), ("g", 36, 4609, 1352, 832, 1, 3),
+               ("g", 48, 6691, 784, 3968, 1, 5), ("b", 128, 300, 320, 192, 3, 4), ("b", 37, 183, 16, 336, 5, 6),
+               ("b", 61, 221, 872, 80, 3, 1)]
+
+
+def test_misaligned_grouped_products_take_the_register_staged_pick():
+    """Misaligned operands run the register-staged kernel: with the tiling that
+    is best for it, not the one picked at the direct-to-LDS costs."""
+    try:
+        ac.adaptcore_init()
+        pytest.skip("a device reports its own workgroups per CU")
+    except ac.AdaptCoreError:
+        pass
+    for kind, G, M, N, K, direct, staged in GROUP_PICKS:
+        if kind == "g":
+            plan, sa = ac.adaptcore_grouped_plan(M, G, N, K, BF16), 0
+        else:
+            plan, sa = ac.adaptcore_batched_plan(G, M, N, K, BF16), M * K
+        for off, lda, stride, want, kernel in [(0, K, K * N, direct, "k_grouped_dl<"), (1, K, K * N, staged, "k_grouped<"),
+                                               (0, K + 1, K * N, staged, "k_grouped<"),
+                                               (0, K, K * N + 4, staged, "k_grouped<")]:
+            got = ac.adaptcore_call_info(plan, A0 + 2 * off, lda, B0, N, stride_a=sa, stride_b=stride)
+            assert (got["variant_key"] >> 4) & 0xFF == want and got["kernels"][0].startswith(kernel), (kind, G, M, N, K, got)

@@ -132,6 +132,38 @@ def test_grouped_direct_to_lds(case, dtype):
             assert ok3 and ok4 and np.array_equal(v3.view(np.uint64), v4.view(np.uint64)), (cfg, sw)
 
 
+# products whose misaligned operands take another tiling than aligned ones
+@pytest.mark.parametrize("off", [0, 1])
+def test_default_grouped_and_batched_plans(off):
+    t = torch()
+    took = set()
+    for counts, rows, N, K in GROUPS + [([60, 200, 40], 300, 440, 344)]:
+        G = len(counts)
+        A = gen.uniform_bf16(rows, K, 5)
+        B = np.concatenate([gen.uniform_bf16(K, N, 6 + g).reshape(-1) for g in range(G)])
+        C_ref, D, cov = grouped_ref.grouped_gemm(A, B, np.asarray(counts, np.int32), rows, N, K, K, N, K * N)
+        plan = ac.adaptcore_grouped_plan(rows, G, N, K, F32)
+        vals, ok = grouped(plan, counts, A, B, rows, G, N, K, F32, off)
+        assert ok and gemm_ref.err_metric(vals[cov], C_ref[cov], D[cov]) <= tol(F32), (counts, N, K)
+        took.add(ac.adaptcore_call_info(plan, 4096 + 2 * off, K, 4096, N, 0, K * N)["variant_key"] !=
+                 ac.adaptcore_plan_info(plan)["variant_key"])
+    for batch, M, N, K in [(37, 183, 16, 336), (3, 1000, 136, 72), (61, 70, 304, 80)]:
+        A = gen.uniform_bf16(batch * M, K, 1)
+        B = gen.uniform_bf16(batch * K, N, 2)
+        Ad, a = to_device(A, K, off)
+        Bd = t.from_numpy(B.view(np.int16)).to("cuda")
+        out = Out(batch * M, N, N, F32)
+        plan = ac.adaptcore_batched_plan(batch, M, N, K, F32)
+        ac.adaptcore_batched_matmul(plan, a, K, M * K, Bd.data_ptr(), N, K * N, out.addr, N, M * N, 0)
+        t.cuda.synchronize()
+        vals, ok = out.read()
+        C_ref, D = grouped_ref.batched_gemm(A.reshape(-1), B.reshape(-1), batch, M, N, K, K, N, M * K, K * N)
+        assert ok and gemm_ref.err_metric(vals, C_ref.reshape(-1, N), D.reshape(-1, N)) <= tol(F32), (batch, M, N, K)
+        took.add(ac.adaptcore_call_info(plan, a, K, Bd.data_ptr(), N, M * K, K * N)["variant_key"] !=
+                 ac.adaptcore_plan_info(plan)["variant_key"])
+    assert (True in took) == (off == 1), took
+
+
 @pytest.mark.parametrize("shape", [(5, 70, 304, 200), (3, 300, 136, 72), (9, 1, 8, 264), (2, 129, 520, 128)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_batched_direct_to_lds(shape):
