@@ -753,9 +753,6 @@ bool group_work(const Ctx& c, int cfg, int swizzle, bool direct, Plan* one, Work
   const int d = kGroupedDl[cfg];
   if (!direct || d < 0 || c.s.K < GROUPED_DL_MIN_K || c.s.K % 8 != 0 || c.s.N % 8 != 0) return true;
   const DlCfg& t = kDlCfg[d];
-  const TileCfg& own = kTileCfg[cfg];
-  const int wm = own.bm >= 128 ? 2 : 1;
-  w->lds_it = (double)(own.bm * (1 + 4 / wm) + own.bn * (1 + wm)) * TILE_BK * 2;  // as build_dl's
   w->idx = IDX_DL + d;
   w->occ = occupancy(FAM_DL, d);
   w->prefetch = (double)(t.stages - 1) * t.bk / TILE_BK;
@@ -1448,7 +1445,7 @@ int config_index(int family, int cfg) {
     case FAM_DLSC:  // the direct-to-LDS configuration's costs (the same tile code)
       return ((cfg & 0xF) == 0 || (cfg & 0xF) == 4) && (cfg >> 4) <= 10 ? IDX_DL + (cfg & 0xF) : -1;
     case FAM_BATCHED:
-    case FAM_GROUPED:  // the register-staged form's: the tile kernel's costs
+    case FAM_GROUPED:  // the tile kernel's costs
       return cfg >= 0 && cfg < N_TILE_CFG && kGroupedCfg[cfg] ? IDX_TILE + cfg : -1;
   }
   return -1;

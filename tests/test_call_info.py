@@ -180,30 +180,6 @@ def test_grouped_forms(dtype):
     assert seen == set(dl)
 
 
-@pytest.mark.parametrize("calibrated", [True, False])
-def test_grouped_price_is_the_direct_to_lds_one(calibrated):
-    """A batch of one product is priced as the direct-to-LDS plan of the same
-    tile, also by the generic terms of a profile without fitted costs."""
-    hw = ac.adaptcore_get_hw()
-    try:
-        if not calibrated:
-            plain = ac.adaptcore_get_hw()
-            for i in range(ac.AC_N_CFG):
-                plain.cfg_iter[i] = plain.cfg_wg[i] = 0.0
-            plain.lds_bw_cu /= 8  # the LDS term decides
-            ac.adaptcore_set_hw(plain)
-        for M, N, K in [(1024, 1024, 512), (4000, 520, 4096), (300, 8192, 200)]:
-            for cfg, d in [(1, 1), (2, 2), (3, 9), (8, 3)]:
-                b = ac.adaptcore_batched_plan_variant(1, M, N, K, BF16, 0, ac.AC_FAMILY_BATCHED | (cfg << 4) | (1 << 12) |
-                                                      (1 << 16) | (BF16 << 48))
-                p = ac.adaptcore_plan_variant(M, N, K, BF16, 0, ac.AC_FAMILY_DL | (d << 4) | (1 << 12) | (1 << 16) |
-                                              (BF16 << 48))
-                want = ac.adaptcore_plan_info(p)["predicted_s"]
-                assert ac.adaptcore_plan_info(b)["predicted_s"] == pytest.approx(want, rel=1e-12), (M, N, K, cfg)
-    finally:
-        ac.adaptcore_set_hw(hw)
-
-
 # (kind, groups, rows, N, K): tile configuration for aligned and for misaligned operands, with the planner's
 # table of workgroups per CU
 GROUP_PICKS = [("g", 64, 8192, 1536, 4096, 2, 3), ("g", 6, 1744, 440, 1344, 5, 6), ("g", 36, 4609, 1352, 832, 1, 3),
