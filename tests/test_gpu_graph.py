@@ -2,7 +2,8 @@
 
 The benchmark times graph replays, and callers capture the library's calls
 too: a plain plan, a split-K plan (partials in the stream's workspace), a
-plan with a column-major B (the prologue copy in the workspace), AddMM with
+plan with a column-major B (read in place, and one element further on, where
+the prologue copies it into the workspace), AddMM with
 beta != 0, a grouped product and a strided batch are captured on one stream
 (workspace reserved beforehand: no allocation under capture) and replayed
 three times, with the program's own eager work between the replays (inputs
@@ -52,17 +53,22 @@ def test_graph_replays_match_the_oracle():
         checks.append((C, dtype, gemm_ref.gemm(A, B), None, (Ad, Bd)))
     assert ac.adaptcore_plan_info(ac.adaptcore_plan(64, 64, 20000, F32))["pk"] > 1
 
-    # column-major B (prologue copy into the workspace)
+    # column-major B: in place, and the prologue copy into the workspace
     M, N, K = 200, 300, 400
     A, B = gen.operands(M, N, K, seed=5)
     Bt = np.ascontiguousarray(B.T)
-    Ad, Bd = _dev(A), _dev(Bt)
-    C = t.empty(M, N, dtype=t.float32, device="cuda")
     plan = ac.adaptcore_plan(M, N, K, F32, ac.AC_LAYOUT_B_COL)
     assert "k_transpose16" in ac.adaptcore_plan_kernels(plan)
-    calls.append(lambda plan=plan, Ad=Ad, Bd=Bd, C=C: ac.adaptcore_matmul(
-        plan, Ad.data_ptr(), 400, Bd.data_ptr(), 400, C.data_ptr(), 300, s.cuda_stream))
-    checks.append((C, F32, layout_ref.gemm_layout(A.reshape(-1), Bt.reshape(-1), M, N, K, K, K, 2), None, (Ad, Bd)))
+    key = ac.adaptcore_plan_info(plan)["variant_key"]
+    for off in (0, 1):
+        Ad, Bd = _dev(A), _dev(np.concatenate([np.zeros(off, np.uint16), Bt.reshape(-1)]))
+        C = t.empty(M, N, dtype=t.float32, device="cuda")
+        plan = forced_plan(M, N, K, F32, key, ac.AC_LAYOUT_B_COL)
+        b = Bd.data_ptr() + 2 * off
+        assert ("k_transpose16" in ac.adaptcore_call_info(plan, Ad.data_ptr(), 400, b, 400)["kernels"]) == (off == 1)
+        calls.append(lambda plan=plan, Ad=Ad, b=b, C=C: ac.adaptcore_matmul(
+            plan, Ad.data_ptr(), 400, b, 400, C.data_ptr(), 300, s.cuda_stream))
+        checks.append((C, F32, layout_ref.gemm_layout(A.reshape(-1), Bt.reshape(-1), M, N, K, K, K, 2), None, (Ad, Bd)))
 
     # AddMM with beta != 0: C is restored before every replay
     M, N, K = 150, 260, 330
