@@ -494,7 +494,8 @@ adaptcore_status adaptcore_call_info(const adaptcore_plan_t* plan, const void* A
                                      const void* B, int64_t ldb, int64_t stride_b, adaptcore_call_desc_t* out);
 
 /* Lists the legal candidates of a shape with their model latencies, ordered
- * by the model's preference (best first). Returns the number of candidates
+ * by the model's preference (best first): by latency, less the copy of a
+ * column-major operand that a configuration reads in place where aligned. Returns the number of candidates
  * (which may exceed cap; at most cap are written), or a negative status. */
 int64_t adaptcore_candidates(int64_t M, int64_t N, int64_t K, int32_t dtype, uint32_t layouts,
                              adaptcore_candidate_t* out, int64_t cap);
