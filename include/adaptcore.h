@@ -317,11 +317,14 @@ adaptcore_status adaptcore_matmul(const adaptcore_plan_t* plan, const void* A, i
  * No call of this entry point allocates or frees device memory. The
  * caller still passes A, B and C; arguments and checks are those of
  * adaptcore_matmul, and a call whose workspace (adaptcore_call_info) exceeds
- * the array gives AC_ERR_UNSUPPORTED (nothing launched). Every call on one GPU shares that
- * GPU's array, and the array keeps the last call's contents: no part of it
- * needs clearing (every byte a call reads was written earlier in the same
- * call), but calls that overlap in time on one GPU (different streams, or
- * the same graph replayed concurrently) race on it -- order them. */
+ * the array gives AC_ERR_UNSUPPORTED (nothing launched), unless the plan was
+ * searched for (adaptcore_plan without an override) and another configuration
+ * of its search fits: the best such one then runs, with its own order of sums.
+ * Every call on one GPU shares that GPU's array, and the array keeps the last
+ * call's contents: no part of it needs clearing (every byte a call reads was
+ * written earlier in the same call), but calls that overlap in time on one GPU
+ * (different streams, or the same graph replayed concurrently) race on it --
+ * order them. */
 adaptcore_status adaptcore_matmul_noalloc(const adaptcore_plan_t* plan, const void* A, int64_t lda, const void* B,
                                           int64_t ldb, void* C, int64_t ldc, void* stream);
 

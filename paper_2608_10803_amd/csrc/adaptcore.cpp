@@ -27,6 +27,9 @@ struct adaptcore_plan_s {
   // Grouped and batched plans: the configuration for operands that the
   // direct-to-LDS kernels do not take, where it is another one.
   std::unique_ptr<ac::Plan> alt;
+  // Where one of the two needs more workspace than the no-allocation scratch
+  // holds: the best configuration that does not, for adaptcore_matmul_noalloc.
+  std::unique_ptr<ac::Plan> fit;
 };
 
 namespace {
@@ -163,11 +166,18 @@ adaptcore_plan_s* plan_miss(const ac::Shape& s) {
   auto* p = new adaptcore_plan_s{c.front()};
   bool exact;
   p->p.shape_key = ac::shape_key(s, &exact);
+  auto less = [](const ac::Plan& a, const ac::Plan& b) {  // with every copy counted
+    return a.predicted != b.predicted ? a.predicted < b.predicted : a.variant_key < b.variant_key;
+  };
   if (p->p.in_place) {
-    const ac::Plan& copied = *std::min_element(c.begin(), c.end(), [](const ac::Plan& a, const ac::Plan& b) {
-      return a.predicted != b.predicted ? a.predicted < b.predicted : a.variant_key < b.variant_key;
-    });
+    const ac::Plan& copied = *std::min_element(c.begin(), c.end(), less);
     if (copied.variant_key != p->p.variant_key) p->alt.reset(new ac::Plan(copied));
+  }
+  if (std::max(p->p.ws_bytes, p->alt ? p->alt->ws_bytes : 0) > ac::NOALLOC_SCRATCH_BYTES) {
+    const ac::Plan* best = nullptr;
+    for (const ac::Plan& q : c)
+      if (q.ws_bytes <= ac::NOALLOC_SCRATCH_BYTES && (!best || less(q, *best))) best = &q;
+    if (best) p->fit.reset(new ac::Plan(*best));
   }
   g_owned.push_back(p);
   st_miss_seconds += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -389,15 +399,8 @@ bool dl_loads(const ac::Plan& p, const void* A, int64_t lda, const void* B, int6
          ((p.s.layouts & AC_LAYOUT_B_COL) || p.ws_b_off >= 0 || ac::dl_b_aligned(B, ldb, p.s.N));
 }
 
-adaptcore_status route_call(const adaptcore_plan_s& plan, const void* A, int64_t lda, const void* B, int64_t ldb,
-                            Route* r) {
-  // A search that counted on reading an operand in place (in_place) took a
-  // configuration which, with that operand copied, may be far from the best:
-  // 4 x 4096 x 14336 with B one element past an aligned address runs in
-  // 58 us on the small-M kernel, which reads such a B, and in 77 us copied.
-  const bool in_place = !plan.alt || (dl_loads(plan.p, A, lda, B, ldb) &&
-                                      (dl_in_place(plan.p, A, lda, B, ldb) & plan.p.in_place) != 0);
-  const ac::Plan& p = in_place ? plan.p : *plan.alt;
+// One configuration on a call's operands.
+adaptcore_status route_config(const ac::Plan& p, const void* A, int64_t lda, const void* B, int64_t ldb, Route* r) {
   const int64_t N = p.s.N, K = p.s.K;
   const bool a_col = (p.s.layouts & AC_LAYOUT_A_COL) != 0, b_col = (p.s.layouts & AC_LAYOUT_B_COL) != 0;
   // Direct-to-LDS plans: operands the plan does not copy must have 16-byte
@@ -462,7 +465,7 @@ adaptcore_status route_call(const adaptcore_plan_s& plan, const void* A, int64_t
     r->run = &r->own;
   }
   const ac::Plan& q = *r->run;
-  if (q.family == ac::FAM_DL && !q.unal) r->lay = dl_in_place(q, A, lda, B, ldb);
+  r->lay = q.family == ac::FAM_DL && !q.unal ? dl_in_place(q, A, lda, B, ldb) : 0;
   // prologue: row-major copies of column-major operands, and zero-padded
   // copies of unaligned row-major operands for the direct loads of a
   // direct-to-LDS plan (rows of K and N rounded up to 8); the register-load
@@ -480,6 +483,18 @@ adaptcore_status route_call(const adaptcore_plan_s& plan, const void* A, int64_t
   r->ws_bytes = r->off_b + (r->copy_b ? q.ws_bytes - q.ws_b_off : 0);
   r->launches = q.n_launch - (q.ws_a_off >= 0) - (q.ws_b_off >= 0) + r->copy_a + r->copy_b;
   return AC_OK;
+}
+
+// A plan's configuration on a call's operands. A search that counted on
+// reading an operand in place (in_place) took one which, with that operand
+// copied, may be far from the best: 4 x 4096 x 14336 with B one element past
+// an aligned address runs in 58 us on the small-M kernel, which reads such a B,
+// and in 77 us copied.
+adaptcore_status route_call(const adaptcore_plan_s& plan, const void* A, int64_t lda, const void* B, int64_t ldb,
+                            Route* r) {
+  const bool in_place = !plan.alt || (dl_loads(plan.p, A, lda, B, ldb) &&
+                                      (dl_in_place(plan.p, A, lda, B, ldb) & plan.p.in_place) != 0);
+  return route_config(in_place ? plan.p : *plan.alt, A, lda, B, ldb, r);
 }
 
 // One call of a plain plan; epi != 0 selects the AddMM epilogue. With
@@ -533,6 +548,8 @@ adaptcore_status run_matmul(const adaptcore_plan_t* plan, const void* A, int64_t
   g.nB = N;
   Route r;
   st = route_call(*plan, A, lda, B, ldb, &r);
+  if (st == AC_OK && fixed && r.ws_bytes > ac::NOALLOC_SCRATCH_BYTES && plan->fit)
+    st = route_config(*plan->fit, A, lda, B, ldb, &r);
   if (st != AC_OK) return st;
   // the launch fields, workspace and prologue of the configuration that runs
   const ac::Plan& q = *r.run;

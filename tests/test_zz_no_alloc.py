@@ -157,6 +157,30 @@ def test_capture_of_decode_weights_needs_the_partials_only():
         _close(C, ref)
 
 
+def test_noalloc_runs_a_configuration_that_fits():
+    """Plans whose workspace (padded copies, partials) exceeds the scratch:
+    the best configuration of the search that fits it runs instead."""
+    t = torch()
+    cap = ac.adaptcore_noalloc_scratch_bytes()
+    over = 0
+    for (M, N, K, dtype) in [(26095, 476, 2819, BF16), (5461, 392, 17806, F32), (20011, 600, 2001, BF16),
+                             (9001, 1500, 6003, F32)]:
+        g = t.Generator(device="cuda").manual_seed(M)
+        A = t.empty(M, K, device="cuda").uniform_(-1, 1, generator=g).bfloat16()
+        B = t.empty(K, N, device="cuda").uniform_(-1, 1, generator=g).bfloat16()
+        plan = ac.adaptcore_plan(M, N, K, dtype)
+        over += ac.adaptcore_call_info(plan, A.data_ptr(), K, B.data_ptr(), N)["workspace_bytes"] > cap
+        C = t.full((M, N), float("nan"), dtype=t.float32 if dtype == F32 else t.bfloat16, device="cuda")
+        ac.adaptcore_matmul_noalloc(plan, A.data_ptr(), K, B.data_ptr(), N, C.data_ptr(), N, 0)
+        t.cuda.synchronize()
+        rows = t.arange(0, M, 97, device="cuda")
+        Ad, Bd = A[rows].double(), B.double()
+        err = gemm_ref.err_metric(_vals(C[rows].contiguous(), dtype), (Ad @ Bd).cpu().numpy(),
+                                  (Ad.abs() @ Bd.abs()).cpu().numpy())
+        assert err <= tol(dtype), (M, N, K, err)
+    assert over >= 2, over
+
+
 def test_noalloc_refuses_a_workspace_beyond_the_scratch():
     t = torch()
     M, N, K = 2048, 2048, 65536
